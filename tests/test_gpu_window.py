@@ -1,0 +1,30 @@
+"""kda_weights at the edges of its token tiles (16 tokens: one, a remainder,
+a whole tile, several) against the oracle's float64 recursion."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2609_30950_amd as K
+import workloads as W
+from oracle import stats
+from tests._gpu import dev, host
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("Wn,C", [(1, 1), (2, 1), (16, 3), (17, 1), (18, 64), (33, 16), (50, 7)])
+@pytest.mark.parametrize("d,per_head,erase", [(64, False, True), (128, True, False), (256, True, True),
+                                              (128, False, False)])
+def test_window_weights_at_tile_edges(Wn, C, d, per_head, erase):
+    B, H = 2, 3
+    w = W.sized(W.WORKLOADS["gdn2" if per_head else "tiny"], B=B, H=H, dk=d, dv=d)
+    x = W.tokens(w, 0, Wn)
+    cfg = K.Config(B=B, H=H, d_k=d, d_v=d, group_rows=d, decay_per_head=int(per_head), no_erase=int(not erase))
+    g = torch.full((B * H * d,), -1.0, dtype=torch.float64, device="cuda")
+    s_arg = x["s"][..., 0] if per_head else x["s"]
+    K.kda_weights(cfg, Wn, C, dev(x["q"]), dev(s_arg), dev(x["beta"]), dev(x["k"]), g)
+    s_full = np.broadcast_to(x["s"], x["k"].shape)
+    want = stats.window_gamma(*(np.moveaxis(a, 1, 0) for a in (x["q"], s_full, x["k"], x["beta"])), C, erase=erase)
+    # sums of non-negative terms in the same order; exp arguments of magnitude
+    # below 10, so each factor agrees within some 20 ulp and 50 of them within 2e-13
+    np.testing.assert_allclose(host(g).reshape(B, H, d), want, rtol=1e-12)
