@@ -301,8 +301,15 @@ __device__ __forceinline__ void stats_head(const KParams& p, int bh, StatsLds<DK
   }
 }
 
+// Waves per SIMD the statistics pass is compiled for.  d_k <= 128: six (80
+// VGPRs, 32 to 64 of them the state), what the LDS of a block allows too.
+// d_k = 256: a lane holds 128 state values and a block is two waves per SIMD,
+// so the register budget is the one of two (six spilled 226 registers a lane:
+// the step took 104 us at B = 16, H = 16 instead of 74).
+constexpr int stats_waves(int dk) { return dk <= 128 ? 6 : 2; }
+
 template <int DK, int DV, bool HEAD, bool BF16>
-__global__ void __launch_bounds__(2 * DK) __attribute__((amdgpu_waves_per_eu(6))) k_chunk(KParams p) {
+__global__ void __launch_bounds__(2 * DK) __attribute__((amdgpu_waves_per_eu(stats_waves(DK)))) k_chunk(KParams p) {
   extern __shared__ uint4 dyn_lds[];
   __shared__ StatsLds<DK, DV> sm;
   uint32_t* words = (uint32_t*)dyn_lds;
