@@ -13,8 +13,9 @@
 //
 // Decode (C = 1) runs three kernels: stats (recurrence, outputs, row ranges,
 // EMA rates, weights), alloc (layer budget per sequence; skipped for the
-// per-head scope, which allocates inside stats) and requant (recompute the
-// recurrence from the record, fit, quantise, pack in place).
+// per-head scope, which allocates inside stats, and for few heads, whose
+// requantisation allocates) and requant (fit, quantise, pack in place, from
+// the state rebuilt out of the record or left by stats: step_writeback).
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -164,11 +165,6 @@ __device__ __forceinline__ void row_rates(const KParams& p, int bh, StatSmem<DK>
   }
 }
 
-// Decode steps of heads with d_k <= 128 hand the requantisation the token's
-// vectors (a, g, w) instead of the float32 state; it rebuilds the state from
-// the record (d_k = 256 would need a larger LDS staging than its code tile).
-constexpr bool compact_decode(int dk) { return dk <= 128; }
-
 // LDS of the statistics pass of one head; the record's code words follow it
 // in the same allocation (and, for the per-head budget, the allocator's
 // scratch once the words are decoded).
@@ -192,12 +188,17 @@ inline size_t stats_dyn_bytes(int wc) {
   return w > sizeof(RecSmem<DK, DV>) ? w : sizeof(RecSmem<DK, DV>);
 }
 
+// What the statistics pass of a decode step leaves for the requantisation: the
+// token's vectors (a, g, w; d_k <= 128), from which it can rebuild the state
+// with the record, the float32 state, or both.
+enum Handover { HAND_VECTORS = 1, HAND_STATE = 2 };
+
 // Decode token tok0 of one head with the state resident in registers,
 // starting from the record: the output o, the token's vectors (d_k <= 128) or
 // the float32 state after it (d_k = 256) for the requantisation, row ranges
 // and EMA rates, weights c and, for the per-head scope, the widths (with
 // alloc_sm as the allocator's LDS).  All threads of the block (2 d_k) call it.
-template <int DK, int DV, bool HEAD, bool BF16, bool COMPACT>
+template <int DK, int DV, bool HEAD, int HAND>
 __device__ __forceinline__ void stats_head(const KParams& p, int bh, StatsLds<DK, DV>& sm,
                                            uint32_t* words, AllocSmem* alloc_sm) {
   const int t = threadIdx.x;
@@ -209,7 +210,7 @@ __device__ __forceinline__ void stats_head(const KParams& p, int bh, StatsLds<DK
   // the first token's row scalars are requested with the metadata; the
   // record's meaningful code words (ceil(sum b / 32) per column) follow once
   // the widths are known
-  RowIn in = load_rows<DK, BF16>(sm.rs, p, bh, p.tok0);
+  RowIn in = load_rows<DK, false>(sm.rs, p, bh, p.tok0);   // decode inputs are float32
   load_meta<DK, DV>(rec, L, p.bmax, meta);
   // up to four 16-byte loads per thread are issued now and written to LDS
   // after the row threads' float64 work below, the rest (means above 8 bits
@@ -258,9 +259,9 @@ __device__ __forceinline__ void stats_head(const KParams& p, int bh, StatsLds<DK
   __syncthreads();
   float X[ROW_BLOCK][DV / WAVE];
   unpack_cols<DK, DV>(words, meta, X);
-  // COMPACT (one token): the requantisation rebuilds the state from the
-  // record and the token's vectors a, g, w; else it reads the float32 state
-  constexpr bool compact = COMPACT;
+  // HAND_VECTORS (one token): the requantisation rebuilds the state from the
+  // record and the token's vectors a, g, w
+  constexpr bool compact = (HAND & HAND_VECTORS) != 0;
   float* hv = p.ws_hv + (size_t)bh * (DV + 2 * DK);
   {
     const int tok = p.tok0;
@@ -271,10 +272,10 @@ __device__ __forceinline__ void stats_head(const KParams& p, int bh, StatsLds<DK
     }
     const size_t th = ((size_t)b * p.T + tok) * p.H + h;
     // the words are decoded (barrier above): their space holds the partials
-    recur_token<DK, DV, BF16>(X, sm.rs, *(RecSmem<DK, DV>*)words, p.v, th * DV, p.o + th * DV, !p.no_erase,
+    recur_token<DK, DV, false>(X, sm.rs, *(RecSmem<DK, DV>*)words, p.v, th * DV, p.o + th * DV, !p.no_erase,
                               compact ? hv : nullptr);
   }
-  if (!compact) {
+  if constexpr ((HAND & HAND_STATE) != 0) {
     // float32 state after the last token, row-major, for the requantisation
     const int w = t / WAVE, lane = lane_id();
     float* dstS = p.ws_s32 + (size_t)bh * DK * DV;
@@ -308,12 +309,12 @@ __device__ __forceinline__ void stats_head(const KParams& p, int bh, StatsLds<DK
 // the step took 104 us at B = 16, H = 16 instead of 74).
 constexpr int stats_waves(int dk) { return dk <= 128 ? 6 : 2; }
 
-template <int DK, int DV, bool HEAD, bool BF16>
+template <int DK, int DV, bool HEAD, int HAND>
 __global__ void __launch_bounds__(2 * DK) __attribute__((amdgpu_waves_per_eu(stats_waves(DK)))) k_chunk(KParams p) {
   extern __shared__ uint4 dyn_lds[];
   __shared__ StatsLds<DK, DV> sm;
   uint32_t* words = (uint32_t*)dyn_lds;
-  stats_head<DK, DV, HEAD, BF16, compact_decode(DK)>(p, blockIdx.x, sm, words, (AllocSmem*)dyn_lds);
+  stats_head<DK, DV, HEAD, HAND>(p, blockIdx.x, sm, words, (AllocSmem*)dyn_lds);
 }
 
 // Layer budget: one block per scope unit of N rows (contiguous in ws_c).
@@ -335,6 +336,14 @@ __global__ void __launch_bounds__(requant_threads(DK, DV, PAIRS, PARTS))
   int bh = blockIdx.x, part = 0;
   if constexpr (PARTS > 1) slice_block(p.B * p.H, PARTS, bh, part);
   requant_head<DK, DV, COMPACT, CodeTile<C8>, PAIRS, PARTS, ALLOC>(p, bh, sm, part);
+}
+
+template <int DK, bool C8, bool ALLOC>
+__global__ void __launch_bounds__(1024) k_requant_par(KParams p) {
+  __shared__ ParLds<DK, CodeTile<C8>> sm;
+  int bh, part;
+  slice_block(p.B * p.H, DK / par_rows<DK>(), bh, part);   // a head's blocks on one XCD
+  requant_par<DK, CodeTile<C8>, ALLOC>(p, bh, part, sm);
 }
 
 // Buffer resource over n bytes at base (word 3 of a gfx9 resource: untyped
@@ -910,6 +919,69 @@ __global__ void __launch_bounds__(1024) k_alloc_slices(KParams p, int N, int nsl
 
 // ------------------------------------------------------- launchers ---
 
+// Requantisation of given float32 states and widths (prefill intervals; decode
+// steps of a middle number of heads).
+static hipError_t launch_chunk_requant(const KParams& p, hipStream_t st) {
+  const int DK = p.dk;
+  // d_v <= 128: the fit evaluates FL candidates of a row segment at once
+  // (FL times the lanes per head; a prefill has few heads, so the grid alone
+  // would leave SIMDs idle, and the rows with the longest candidate scans
+  // would set the time of the block) and two blocks share each head (rows
+  // split in halves)
+  constexpr int FL = 4, PT = 2;
+  const bool c8 = DK > 128 || p.bmax <= 8;
+  constexpr int T64 = requant_threads(64, 64, FL, PT), T128 = requant_threads(128, 128, FL, PT);
+  const int nblk = p.B * p.H * PT;
+  if (DK == 64)
+    return c8 ? launch("requant", k_requant<64, 64, false, true, FL, PT>, nblk, T64, 0, st, p)
+              : launch("requant", k_requant<64, 64, false, false, FL, PT>, nblk, T64, 0, st, p);
+  if (DK == 256) return launch("requant", k_requant<256, 256, false, true>, p.B * p.H, 512, 0, st, p);
+  return c8 ? launch("requant", k_requant<128, 128, false, true, FL, PT>, nblk, T128, 0, st, p)
+            : launch("requant", k_requant<128, 128, false, false, FL, PT>, nblk, T128, 0, st, p);
+}
+
+// How a decode step is written back, by the size of the grid.  A block that
+// takes a whole head and scans the clip factors in turn (k_requant on the
+// rebuilt state) needs 20 us for one round of blocks, nearly all of it latency;
+// with few heads the chip has room for more lanes per row:
+//  * WB_PAR: one lane per factor (k_requant_par, which then also selects the
+//    widths) while its blocks fit one per compute unit (256): 10 to 12 us; each
+//    further round costs as much again.  d_k = 256: up to three rounds, with a
+//    separate allocation from the second on, since there a head takes 46 us.
+//  * WB_QUAD (d_k <= 128): four lanes per factor group and two blocks per head
+//    (as the prefill) up to a float32 state of 16 MB: 13 us at 64 to 256 heads
+//    of 128; from the next head on the compact form is the faster one.
+//  * WB_COMPACT / WB_HEAD: a block per head, the state rebuilt from the record
+//    (d_k <= 128) or read (256).
+// Whole steps, us, at a four-bit mean, COMPACT/HEAD, QUAD, PAR:
+//   d 128, heads 32: 36.6 28.4 22.3   64: 36.6 28.6 22.7   96: 36.7 29.1 32.8
+//          128: 36.9 29.4 33.2   256: 37.0 36.0 54.8   288: 43.6 43.8 66.3
+//   d  64, heads 32: 35.2 23.4 19.2   256: 34.0 27.2 21.6   384: 38.5 28.0 30.8
+//          1024: 39.9 33.7 51.7   2048: 52.9 52.7 93.1
+//   d 256, heads 32: 58.5 - 31.7   64: 60.6 - 43.8   96: 62.6 - 53.8   128: 64.5 - 65.1
+enum WriteBack { WB_COMPACT, WB_HEAD, WB_QUAD, WB_PAR };
+template <int DK>
+static WriteBack step_writeback(const KParams& p) {
+  const int nbh = p.B * p.H;
+  if (p.ws_s32 == nullptr) return WB_COMPACT;   // scratch without room for a float32 state
+  const int par_blocks = nbh * (DK / par_rows<DK>());
+  if (par_blocks <= 256 * (DK == 256 ? 3 : 1)) return WB_PAR;
+  if (DK == 256) return WB_HEAD;
+  return (long long)nbh * DK * DK <= (4 << 20) ? WB_QUAD : WB_COMPACT;
+}
+
+// The statistics pass of a decode step.
+template <int DK, int DV, int HAND>
+static hipError_t launch_stats(const KParams& p, hipStream_t st) {
+  const int nbh = p.B * p.H;
+  // code-word staging; with the per-head budget the allocator's scratch
+  // reuses it after the words are decoded
+  size_t dyn = stats_dyn_bytes<DK, DV>(p.L.wc);
+  if (p.scope == 1 && dyn < sizeof(AllocSmem)) dyn = sizeof(AllocSmem);
+  return p.scope == 1 ? launch("stats", k_chunk<DK, DV, true, HAND>, nbh, 2 * DK, dyn, st, p)
+                      : launch("stats", k_chunk<DK, DV, false, HAND>, nbh, 2 * DK, dyn, st, p);
+}
+
 // One write-back interval: tokens [p.tok0, p.tok0 + p.ntk), then quantise.
 // phases: 1 = stats and allocation, 2 = requantisation, 3 = both.
 template <int DK, int DV>
@@ -924,20 +996,15 @@ static hipError_t launch_interval_t(const KParams& p, hipStream_t st, int phases
     return p.in_bf16 ? launch("step32", k_step32<DK, DV, true, false>, nblk, 2 * DK, 0, st, p)
                      : launch("step32", k_step32<DK, DV, false, false>, nblk, 2 * DK, 0, st, p);
   }
+  const WriteBack wb = step_writeback<DK>(p);
+  const int par_blocks = nbh * (DK / par_rows<DK>());
+  const bool alloc_in = wb == WB_PAR && par_blocks <= 256 && p.scope == 0 && p.G <= DK;
   hipError_t e = hipSuccess;
   if (phases & 1) {
-    // code-word staging; with the per-head budget the allocator's scratch
-    // reuses it after the words are decoded
-    size_t dyn = stats_dyn_bytes<DK, DV>(p.L.wc);
-    if (p.scope == 1 && dyn < sizeof(AllocSmem)) dyn = sizeof(AllocSmem);
-    if (p.scope == 1)
-      e = p.in_bf16 ? launch("stats", k_chunk<DK, DV, true, true>, nbh, 2 * DK, dyn, st, p)
-                    : launch("stats", k_chunk<DK, DV, true, false>, nbh, 2 * DK, dyn, st, p);
-    else
-      e = p.in_bf16 ? launch("stats", k_chunk<DK, DV, false, true>, nbh, 2 * DK, dyn, st, p)
-                    : launch("stats", k_chunk<DK, DV, false, false>, nbh, 2 * DK, dyn, st, p);
+    e = wb == WB_COMPACT ? launch_stats<DK, DV, HAND_VECTORS>(p, st)
+                         : launch_stats<DK, DV, DK <= 128 ? HAND_VECTORS | HAND_STATE : HAND_STATE>(p, st);
     if (e != hipSuccess) return e;
-    if (p.scope == 0) {
+    if (p.scope == 0 && !alloc_in) {
       if (p.G > DK)   // groups spanning heads: weights from the row maxima and Gamma
         e = launch("alloc", k_alloc_slices, p.B, 1024, 0, st, p, p.H * DK, 1,
                    (const float*)p.ws_rpart, (const double*)p.ws_gam, p.ws_bits);
@@ -948,9 +1015,21 @@ static hipError_t launch_interval_t(const KParams& p, hipStream_t st, int phases
     }
   }
   if (!(phases & 2)) return hipSuccess;
-  if (DK > 128 || p.bmax <= 8)
-    return launch("requant", k_requant<DK, DV, compact_decode(DK), true>, nbh, 2 * DK, 0, st, p);
-  return launch("requant", k_requant<DK, DV, compact_decode(DK), (DK > 128)>, nbh, 2 * DK, 0, st, p);
+  const bool c8 = DK > 128 || p.bmax <= 8;
+  if (wb == WB_PAR) {
+    if (alloc_in)
+      return c8 ? launch("requant", k_requant_par<DK, true, true>, par_blocks, 1024, 0, st, p)
+                : launch("requant", k_requant_par<DK, (DK > 128), true>, par_blocks, 1024, 0, st, p);
+    return c8 ? launch("requant", k_requant_par<DK, true, false>, par_blocks, 1024, 0, st, p)
+              : launch("requant", k_requant_par<DK, (DK > 128), false>, par_blocks, 1024, 0, st, p);
+  }
+  if constexpr (DK > 128) {
+    return launch("requant", k_requant<DK, DV, false, true>, nbh, 2 * DK, 0, st, p);
+  } else {
+    if (wb == WB_QUAD) return launch_chunk_requant(p, st);
+    return c8 ? launch("requant", k_requant<DK, DV, true, true>, nbh, 2 * DK, 0, st, p)
+              : launch("requant", k_requant<DK, DV, true, false>, nbh, 2 * DK, 0, st, p);
+  }
 }
 
 static hipError_t launch_interval(const KParams& p, hipStream_t st, int phases = 3) {
@@ -989,25 +1068,6 @@ static hipError_t launch_chunk_alloc(const KParams& p, int nsl, hipStream_t st, 
     return launch("alloc", k_alloc, units, 1024, 0, st, p.ws_c, N, p.need, p.bmin, p.bmax, p.ws_bits);
   return launch("alloc", k_alloc_slices, units, 1024, 0, st, p, N, nsl,
                 (const float*)p.ws_rpart, (const double*)p.ws_gam, p.ws_bits);
-}
-
-static hipError_t launch_chunk_requant(const KParams& p, hipStream_t st) {
-  const int DK = p.dk;
-  // d_v <= 128: the fit evaluates FL candidates of a row segment at once
-  // (FL times the lanes per head; a prefill has few heads, so the grid alone
-  // would leave SIMDs idle, and the rows with the longest candidate scans
-  // would set the time of the block) and two blocks share each head (rows
-  // split in halves)
-  constexpr int FL = 4, PT = 2;
-  const bool c8 = DK > 128 || p.bmax <= 8;
-  constexpr int T64 = requant_threads(64, 64, FL, PT), T128 = requant_threads(128, 128, FL, PT);
-  const int nblk = p.B * p.H * PT;
-  if (DK == 64)
-    return c8 ? launch("requant", k_requant<64, 64, false, true, FL, PT>, nblk, T64, 0, st, p)
-              : launch("requant", k_requant<64, 64, false, false, FL, PT>, nblk, T64, 0, st, p);
-  if (DK == 256) return launch("requant", k_requant<256, 256, false, true>, p.B * p.H, 512, 0, st, p);
-  return c8 ? launch("requant", k_requant<128, 128, false, true, FL, PT>, nblk, T128, 0, st, p)
-            : launch("requant", k_requant<128, 128, false, false, FL, PT>, nblk, T128, 0, st, p);
 }
 
 hipError_t launch_chunk_writeback(const KParams& p, int nsl, hipStream_t st, bool keys) {

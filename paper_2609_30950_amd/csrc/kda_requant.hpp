@@ -345,9 +345,11 @@ __device__ __forceinline__ void fit_rows(LoadRow load_row, const uint8_t* bits, 
 // the range (a neighbouring block's) is written with an atomic AND that
 // clears this block's bits and an atomic OR that sets them, so the two
 // blocks' writes commute; words the block owns entirely are plain stores.
-template <int DK, int DV, int ROWS = DK, typename CT>
+// Ct holds rows ct0 on, LD codes per column.
+template <int DK, int DV, int ROWS = DK, int LD_ = 0, typename CT>
 __device__ __forceinline__ void pack_cols(const CT* Ct, const uint8_t* bits, const int* P,
-                                          uint32_t* words, uint32_t* tail, int r0 = 0) {
+                                          uint32_t* words, uint32_t* tail, int r0 = 0, int ct0 = 0) {
+  constexpr int LD = LD_ ? LD_ : ct_ld<DK, CT>();
   constexpr int HALF = ROWS / 2;
   static_assert(DV == DK && DV % WAVE == 0, "one (column, half) per thread, halves wave-aligned");
   const int tid = threadIdx.x;
@@ -383,7 +385,7 @@ __device__ __forceinline__ void pack_cols(const CT* Ct, const uint8_t* bits, con
   constexpr int CB = (int)sizeof(CT);   // bytes per code
   constexpr int CPR = 16 / CB;                  // codes per 16-byte read
   static_assert(HALF % CPR == 0, "whole 16-byte code reads per half");
-  const CT* cc = Ct + (size_t)col * ct_ld<DK, CT>() + a;
+  const CT* cc = Ct + (size_t)col * LD + (a - ct0);
   const bool shared = (split & 31) != 0;
   if (packer) {
 #pragma unroll
@@ -645,5 +647,191 @@ __device__ __forceinline__ void requant_head(const KParams& p, int bh, RequantLd
 // Code tile element: bytes when widths fit (b_max <= 8), else 16 bits.
 template <bool C8>
 using CodeTile = typename std::conditional<C8, int8_t, int16_t>::type;
+
+// ------------------------------- requantisation of few heads (latency) ---
+//
+// The same write-back for grids that leave most of the chip idle when a block
+// takes a head (or half of one): one lane evaluates one of the 16 clip
+// factors of a 64-column segment, so the search is a single step of 64
+// elements per lane instead of up to 16 in turn, and a head is spread over
+// d_k / RQ_ROWS blocks of 1024 threads.  All factors are evaluated (the
+// exhaustive search the pruned scans equal): 1.6 times the instructions of the
+// pruned search at d = 128, so only where the chip has room for them.  The
+// rows come from the float32 state of the statistics pass, in row order.
+//
+// ALLOC as in requant_head.
+
+template <int DK>
+constexpr int par_rows() { return DK == 64 ? 64 : 32; }   // rows per block
+
+template <int DK, typename CT>
+struct ParLds {
+  static constexpr int ROWS = par_rows<DK>(), LD = ROWS + 16 / (int)sizeof(CT);
+  static constexpr int SROW = DK + 4 * (DK / SEG);
+  union {
+    AllocSmem al;
+    __align__(16) CT Ct[DK * LD];   // codes, column-major, rows of the block
+  };
+  __align__(16) float sx[ROWS * SROW];   // rows, segments SEG + 4 floats apart
+  __align__(16) uint8_t nb[DK];
+  int P[DK + 1];
+  int wtot[DK / WAVE];
+  uint16_t sc16[DK], zz[DK], rr[DK];
+  float phi[MAX_B + 1][N_FIT];
+  uint32_t tail[DK];
+};
+
+// Lexicographic minimum of (err, m) with the lane CTRL pairs this one with.
+template <int CTRL>
+__device__ __forceinline__ void best_merge(float& err, int& m) {
+  const float oe = dpp_f<CTRL>(err);
+  const int om = dpp_i<CTRL>(m);
+  const bool take = oe < err || (oe == err && om < m);
+  err = take ? oe : err;
+  m = take ? om : m;
+}
+
+// Sum over the SEGS segments of a row, 16 lanes apart, in the halving order.
+template <int SEGS>
+__device__ __forceinline__ float seg_combine_16(float v) {
+  if constexpr (SEGS == 4) {
+    const int vi = __builtin_bit_cast(int, v);
+    const auto a = __builtin_amdgcn_permlane32_swap(vi, vi, false, false);
+    v = __builtin_bit_cast(float, (int)a[0]) + __builtin_bit_cast(float, (int)a[1]);
+  }
+  if constexpr (SEGS >= 2) {
+    const int vi = __builtin_bit_cast(int, v);
+    const auto c = __builtin_amdgcn_permlane16_swap(vi, vi, false, false);
+    v = __builtin_bit_cast(float, (int)c[0]) + __builtin_bit_cast(float, (int)c[1]);
+  }
+  return v;
+}
+
+template <int DK, typename CT, bool ALLOC>
+__device__ __forceinline__ void requant_par(const KParams& p, int bh, int part, ParLds<DK, CT>& sm) {
+  constexpr int DV = DK, SEGS = DV / SEG, ROWS = par_rows<DK>(), NT = 1024;
+  constexpr int SROW = ParLds<DK, CT>::SROW, LD = ParLds<DK, CT>::LD;
+  constexpr int NV = ROWS * DV / 4 / NT, ITERS = ROWS * SEGS * N_FIT / NT;
+  static_assert(NV >= 1 && ITERS >= 1 && NV * NT * 4 == ROWS * DV && ITERS * NT == ROWS * SEGS * N_FIT,
+                "whole float4 and items per thread");
+  const int t = threadIdx.x, r0 = part * ROWS;
+  const Layout L = p.L;
+  uint8_t* rec = (uint8_t*)slot_ptr(p.records, L.slot, bh);
+  const unsigned ntok = *(const unsigned*)rec;
+  typedef float v4f __attribute__((ext_vector_type(4)));
+  v4f sv[NV];
+  {
+    const v4f* S4 = (const v4f*)(p.ws_s32 + ((size_t)bh * DK + r0) * DV);
+#pragma unroll
+    for (int q = 0; q < NV; ++q) sv[q] = S4[t + q * NT];
+  }
+  const uint32_t zr = t < DK ? p.ws_zr[(size_t)bh * DK + t] : 0u;
+  if constexpr (ALLOC) {
+    const int N = p.H * DK, unit = bh / p.H, row0 = (bh % p.H) * DK;
+    block_allocate<ALLOC_MAX_N / NT>([&](int n) { return p.ws_c[(size_t)unit * N + n]; }, N, p.need, p.bmin,
+                                     p.bmax, sm.nb, sm.al, row0, row0 + DK);
+    __syncthreads();   // the widths are in nb; the allocator's space is free
+  } else if (t < DK) {
+    sm.nb[t] = (uint8_t)min(max((int)p.ws_bits[(size_t)bh * DK + t], 1), p.bmax);
+  }
+  if (t < DK) {
+    sm.zz[t] = (uint16_t)(zr & 0xffffu);
+    sm.rr[t] = (uint16_t)(zr >> 16);
+  }
+#pragma unroll
+  for (int q = 0; q < NV; ++q) {
+    const int e = 4 * (t + q * NT), r = e / DV, c = e % DV;
+    *(v4f*)&sm.sx[r * SROW + c + 4 * (c / SEG)] = sv[q];
+  }
+  for (int e = t; e < (MAX_B + 1) * N_FIT; e += NT) sm.phi[e / N_FIT][e % N_FIT] = p.phi[e / N_FIT][e % N_FIT];
+  // bit offsets of the rows: wave totals now, the sums over waves below
+  int incl = 0;
+  if (t < DK) {
+    incl = wave_incl_scan((int)sm.nb[t]);   // this thread's own store (or after the allocator's barrier)
+    if (lane_id() == WAVE - 1) sm.wtot[t / WAVE] = incl;
+  }
+  __syncthreads();
+  if (t < DK) {
+    for (int q = 0; q < t / WAVE; ++q) incl += sm.wtot[q];
+    sm.P[t + 1] = incl;
+    if (t == 0) sm.P[0] = 0;
+  }
+#pragma unroll
+  for (int rep = 0; rep < ITERS; ++rep) {
+    const int item = rep * (NT / N_FIT) + t / N_FIT, q = t % N_FIT;
+    const int lr = item / SEGS, sg = item % SEGS, i = r0 + lr;
+    const float* xs = &sm.sx[lr * SROW + sg * (SEG + 4)];
+    float x[SEG];
+#pragma unroll
+    for (int u = 0; u < SEG / 4; ++u) {
+      const float4 v = ((const float4*)xs)[u];
+      x[4 * u] = v.x;
+      x[4 * u + 1] = v.y;
+      x[4 * u + 2] = v.z;
+      x[4 * u + 3] = v.w;
+    }
+    const int b = sm.nb[i];
+    const float4 xq = ((const float4*)xs)[q];   // the four columns this lane codes
+    const float xw[4] = {xq.x, xq.y, xq.z, xq.w};
+    CT* dst = sm.Ct + (size_t)(sg * SEG + 4 * q) * LD + lr;
+    if (b == 1) {
+      float acc = 0.f;
+#pragma unroll
+      for (int j = 0; j < SEG; ++j) acc = acc + fabsf(x[j]);
+      acc = seg_combine_16<SEGS>(acc);
+      const uint16_t mu = f32_to_f16_sat(acc * (1.0f / (float)DV));
+#pragma unroll
+      for (int j = 0; j < 4; ++j) dst[(size_t)j * LD] = (CT)(xw[j] < 0.f ? 1 : 0);
+      if (sg == 0 && q == 0) sm.sc16[i] = mu;
+    } else {
+      float mx = 0.f;
+#pragma unroll
+      for (int j = 0; j < SEG; ++j) mx = fmaxf(mx, fabsf(x[j]));
+      if constexpr (SEGS >= 2) mx = fmaxf(mx, __shfl_xor(mx, 16));
+      if constexpr (SEGS == 4) mx = fmaxf(mx, __shfl_xor(mx, 32));
+      const float nf = (float)((1 << (b - 1)) - 1);
+      const float d = f16_to_f32(f32_to_f16_sat_nonneg(mx * sm.phi[b][q]));
+      const float inv = recip_f16_value(d);
+      float err = 0.f;
+#pragma unroll
+      for (int j = 0; j < SEG; ++j) {
+        const float c = __builtin_amdgcn_fmed3f(__builtin_rintf(x[j] * inv), -nf, nf);
+        const float e = __builtin_fmaf(-c, d, x[j]);
+        err = __builtin_fmaf(e, e, err);
+      }
+      err = seg_combine_16<SEGS>(err);
+      // smallest error, the smallest factor among equal ones; a NaN never
+      // wins, and where all are NaN the largest factor is kept
+      int m = q;
+      if (err != err) {
+        err = __builtin_inff();
+        m = 2 * N_FIT;
+      }
+      best_merge<0xB1>(err, m);    // quad permutes, then the mirrors of 8 and 16 lanes
+      best_merge<0x4E>(err, m);
+      best_merge<0x141>(err, m);
+      best_merge<0x140>(err, m);
+      m = min(m, N_FIT - 1);
+      const uint16_t dh = f32_to_f16_sat_nonneg(mx * sm.phi[b][m]);
+      const float db = f16_to_f32(dh), ib = recip_f16_value(db);
+      constexpr float M = 12582912.0f;   // codes as the low bits of M + c (fit_rows)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const float c = __builtin_amdgcn_fmed3f(xw[j] * ib + M, M - nf, M + nf);
+        dst[(size_t)j * LD] = (CT)__builtin_bit_cast(uint32_t, c);
+      }
+      if (sg == 0 && q == 0) sm.sc16[i] = dh;
+    }
+  }
+  if (p.diag_fit != nullptr && lane_id() == 0) {
+    // profiling: every segment and factor of rows wider than one bit
+    int n = 0;
+    for (int i = r0 + t / WAVE; i < r0 + ROWS; i += NT / WAVE) n += sm.nb[i] > 1 ? SEGS * N_FIT : 0;
+    atomicAdd(p.diag_fit, (unsigned long long)n);
+  }
+  __syncthreads();
+  pack_cols<DK, DV, ROWS, LD>(sm.Ct, sm.nb, sm.P, (uint32_t*)(rec + L.codes_off), sm.tail, r0, r0);
+  store_meta<DK, ROWS>(rec, L, ntok + (unsigned)p.ntk, sm.nb, sm.sc16, sm.zz, sm.rr, r0);
+}
 
 }  // namespace kda
