@@ -514,7 +514,7 @@ __device__ __forceinline__ void recur_slice(float (&X)[ROW_BLOCK][1], PfSmem<DK>
   ps.op[j][w][lane] = acc;
 }
 
-template <int DK, bool BF16>
+template <int DK>   // prefill inputs are bf16
 __global__ void __launch_bounds__(2 * DK) k_chunk_slices(KParams p) {
   constexpr int TS = pf_tokens<DK>();
   const int nsl = p.dv / SLICE;
@@ -560,8 +560,8 @@ __global__ void __launch_bounds__(2 * DK) k_chunk_slices(KParams p) {
         const int j = 2 * q + jt;
         const size_t th = ((size_t)b * p.T + p.tok0 + j0 + min(j, nt - 1)) * p.H + h;
         sv[q] = p.per_head ? p.s[th] : p.s[th * DK + i];
-        kv[q] = in_f32<BF16>(p.k, th * DK + i);
-        qv[q] = in_f32<BF16>(p.q, th * DK + i);
+        kv[q] = in_f32<true>(p.k, th * DK + i);
+        qv[q] = in_f32<true>(p.q, th * DK + i);
         bt[q] = p.beta[th];
       }
 #pragma unroll
@@ -577,7 +577,7 @@ __global__ void __launch_bounds__(2 * DK) k_chunk_slices(KParams p) {
     for (int e = t; e < nt * SLICE; e += blockDim.x) {
       const int j = e / SLICE, c = e % SLICE;
       const size_t th = ((size_t)b * p.T + p.tok0 + j0 + j) * p.H + h;
-      ps.v[j][c] = in_f32<BF16>(p.v, th * p.dv + sl * SLICE + c);
+      ps.v[j][c] = in_f32<true>(p.v, th * p.dv + sl * SLICE + c);
     }
     __syncthreads();
     if (ema_here) {
@@ -663,31 +663,39 @@ __device__ __forceinline__ float rowblock_max(float v) {
   return v;
 }
 
+//
+// A block is d_k / 32 waves that run the recurrence and as many that feed them:
+// these form the row scalars of the next TS tokens (with the float64
+// exponentials) and v in LDS, carry the EMA statistics (slice 0) and store the
+// previous tokens' outputs, in buffers by batch parity with one barrier per
+// batch.  At few sequences a SIMD holds one wave of the recurrence, which
+// issues an instruction every 4.9 cycles at best (128 per token); the staging
+// between its tokens, and the row scalars of a token read from LDS just before
+// their use, took as long again: 1550 -> 995 cycles per token, 50.8 -> 38.4 us
+// per 64 tokens at B = 4, H = 32, d_k = 128.
 template <int DK>
 struct PcSmem {
-  static constexpr int TS = 16;
+  static constexpr int TS = 8;
   static constexpr int NRB = DK / ROW_BLOCK;
-  float4 rq[TS][DK];        // {fl32(exp(-s)), k, fl32(beta k), q} of (token, row)
-  double z[TS][DK];         // exp(-2 s): EMA decay samples (slice 0)
-  float beta[TS];
-  float v[TS][SLICE];
-  float o[TS][SLICE];
+  float4 rq[2][TS][DK];     // {fl32(exp(-s)), k, fl32(beta k), q} of (token, row)
+  float v[2][TS][SLICE];
+  float o[2][TS][SLICE];
   float Rw[NRB][DK];        // row maxima of each wave's columns
 };
 
-template <int DK, bool BF16>
-__global__ void __launch_bounds__(2 * DK) k_chunk_cols(KParams p) {
-  constexpr int NRB = DK / ROW_BLOCK;       // row blocks = waves per block
+template <int DK>   // prefill inputs are bf16
+__global__ void __launch_bounds__(4 * DK) __attribute__((amdgpu_waves_per_eu(4))) k_chunk_cols(KParams p) {
+  constexpr int NRB = DK / ROW_BLOCK;       // row blocks = recurrence waves per block
   constexpr int CPW = WAVE / NRB;           // columns per wave
   constexpr int TS = PcSmem<DK>::TS;
-  constexpr int NQ = TS / 2;                // tokens staged per thread and batch
-  constexpr int NV = TS * SLICE / (2 * DK); // values of v staged per thread and batch
+  constexpr int NF = 2 * DK;                // feeding threads (the upper half of the block)
+  constexpr int NV = TS * SLICE / NF;       // values of v per feeding thread and batch
   static_assert(NRB * CPW == SLICE && CPW >= 16, "16-lane DPP rows inside a row block");
   const int nsl = p.dv / SLICE;
   int bh, sl;
   slice_block(p.B * p.H, nsl, bh, sl);   // a head's slices on one XCD
-  const int t = threadIdx.x, w = t / WAVE, lane = lane_id();
-  const int rb = lane / CPW, col = w * CPW + lane % CPW;   // slice-local column
+  const int t = threadIdx.x, w = __builtin_amdgcn_readfirstlane(t / WAVE), lane = lane_id();
+  const bool feeds = w >= NRB;
   const int b = bh / p.H, h = bh % p.H;
   const Layout L = p.L;
   const uint8_t* rec = slot_ptr(p.records, L.slot, bh);
@@ -695,53 +703,74 @@ __global__ void __launch_bounds__(2 * DK) k_chunk_cols(KParams p) {
   __shared__ PcSmem<DK> ps;
   extern __shared__ uint4 dyn_lds[];
   uint32_t* words = (uint32_t*)dyn_lds;
-  // token inputs of one batch in registers: thread t holds row t % DK of
-  // tokens 2q + t / DK, and NV values of v; the next batch's loads are in
-  // flight while the current batch runs
-  const int si = t % DK, sj = t / DK;
-  float sv[NQ], kv[NQ], qv[NQ], bt[NQ], vv[NV];
-  auto issue = [&](int j0) {
-    const int nt = min(TS, p.ntk - j0);
+  const bool erase = !p.no_erase;
+
+  // Feeding thread f = t - 2 d_k holds row f % d_k of a batch's tokens: of all
+  // of them in slice 0 (its second half carries the EMA of the same rows), of
+  // every other one elsewhere.
+  const int f = t - NF, fi = f % DK, fh = f / DK;
+  const bool ema = feeds && sl == 0 && fh == 1;
+  const int j1 = sl == 0 ? 0 : fh, dj = sl == 0 ? 1 : 2;
+  float sv[TS], kv[TS], qv[TS], bt[TS], vv[NV];
+  auto token = [&](int j) { return ((size_t)b * p.T + p.tok0 + j) * p.H + h; };
+  auto issue = [&](int j0) {   // requests of the batch at j0 (tokens past the end: the last one)
 #pragma unroll
-    for (int q = 0; q < NQ; ++q) {
-      const int j = 2 * q + sj;
-      const size_t th = ((size_t)b * p.T + p.tok0 + j0 + min(j, nt - 1)) * p.H + h;
-      sv[q] = p.per_head ? p.s[th] : p.s[th * DK + si];
-      kv[q] = in_f32<BF16>(p.k, th * DK + si);
-      qv[q] = in_f32<BF16>(p.q, th * DK + si);
-      bt[q] = p.beta[th];
-    }
-#pragma unroll
-    for (int u = 0; u < NV; ++u) {
-      const int e = t + u * (2 * DK), j = e / SLICE, c = e % SLICE;
-      const size_t th = ((size_t)b * p.T + p.tok0 + j0 + min(j, nt - 1)) * p.H + h;
-      vv[u] = in_f32<BF16>(p.v, th * p.dv + sl * SLICE + c);
-    }
-  };
-  auto stage = [&](int nt) {
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) {
-      const int j = 2 * q + sj;
-      if (j < nt) {
-        ps.rq[j][si] = make_float4((float)exp(-(double)sv[q]), kv[q], bt[q] * kv[q], qv[q]);
-        if (sl == 0) ps.z[j][si] = decay_sample(sv[q]);
-        if (si == 0) ps.beta[j] = bt[q];
+    for (int q = 0; q < TS; ++q) {
+      const int j = j1 + q * dj;
+      if (j < TS) {
+        const size_t th = token(min(j0 + j, p.ntk - 1));
+        sv[q] = p.per_head ? p.s[th] : p.s[th * DK + fi];
+        kv[q] = in_f32<true>(p.k, th * DK + fi);
+        qv[q] = in_f32<true>(p.q, th * DK + fi);
+        bt[q] = p.beta[th];
       }
     }
 #pragma unroll
     for (int u = 0; u < NV; ++u) {
-      const int e = t + u * (2 * DK);
-      ps.v[e / SLICE][e % SLICE] = vv[u];
+      const int e = f + u * NF;
+      vv[u] = in_f32<true>(p.v, token(min(j0 + e / SLICE, p.ntk - 1)) * p.dv + sl * SLICE + e % SLICE);
     }
   };
-  auto write_o = [&](int j0, int nt) {
-    for (int e = t; e < nt * SLICE; e += blockDim.x) {
-      const int j = e / SLICE, c = e % SLICE;
-      const size_t th = ((size_t)b * p.T + p.tok0 + j0 + j) * p.H + h;
-      p.o[th * p.dv + sl * SLICE + c] = ps.o[j][c];
+  double m_run = 0.0, e_run = 0.0;
+  bool fresh = false;
+  auto stage = [&](int j0, int buf) {
+    if (ema) {
+      // token-sequential EMA of row fi (the first token initialises a fresh record)
+      const int nt = min(TS, p.ntk - j0);
+#pragma unroll
+      for (int q = 0; q < TS; ++q) {
+        if (q >= nt) break;
+        const double zs = decay_sample(sv[q]);
+        const double ys = erase ? erase_sample(kv[q], bt[q]) : 0.0;
+        if (fresh) {
+          m_run = zs;
+          e_run = ys;
+        } else {
+          m_run = p.one_minus_alpha * m_run + p.alpha * zs;
+          e_run = p.one_minus_alpha * e_run + p.alpha * ys;
+        }
+        fresh = false;
+      }
+    } else {
+#pragma unroll
+      for (int q = 0; q < TS; ++q) {
+        const int j = j1 + q * dj;
+        if (j < TS) ps.rq[buf][j][fi] = make_float4((float)exp(-(double)sv[q]), kv[q], bt[q] * kv[q], qv[q]);
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < NV; ++u) {
+      const int e = f + u * NF;
+      ps.v[buf][e / SLICE][e % SLICE] = vv[u];
     }
   };
-  if (p.ntk > 0) issue(0);
+  auto write_o = [&](int j0, int buf) {
+    const int nt = min(TS, p.ntk - j0);
+    for (int e = f; e < nt * SLICE; e += NF)
+      p.o[token(j0 + e / SLICE) * p.dv + sl * SLICE + e % SLICE] = ps.o[buf][e / SLICE][e % SLICE];
+  };
+
+  if (feeds && p.ntk > 0) issue(0);
   {
     // the slice's code words: word kw of column sl*64 + c at words[kw*64 + c]
     const uint4* src = (const uint4*)(rec + L.codes_off);
@@ -751,96 +780,102 @@ __global__ void __launch_bounds__(2 * DK) k_chunk_cols(KParams p) {
       ((uint4*)words)[e] = src[(size_t)(e / Q) * (p.dv / 4) + sl * Q + e % Q];
   }
   load_meta<DK, SLICE>(rec, L, p.bmax, meta);   // its barrier covers the staging
-  float X[ROW_BLOCK][1];
-  // decode rows 32 rb + r of this lane's column: descriptors per lane (the
-  // row blocks of a wave differ), x^ = (code + add) mul as in unpack_cols
-#pragma unroll
-  for (int r = 0; r < ROW_BLOCK; ++r) {
-    const uint4 d = meta.desc[rb * ROW_BLOCK + r];
-    const int sh = (int)(d.y & 31u), bw = (int)(d.y >> 8);
-    const uint32_t lo = words[d.x + col], hi = words[d.x + SLICE + col];
-    const int code = __builtin_amdgcn_sbfe((int)__builtin_amdgcn_alignbit(hi, lo, (uint32_t)sh), 0, bw);
-    X[r][0] = ((float)code + __builtin_bit_cast(float, d.w)) * __builtin_bit_cast(float, d.z);
-  }
-  const bool ema_here = sl == 0 && t < DK;
-  const bool fresh0 = meta.ntok == 0;
-  double m_run = 0.0, e_run = 0.0;
-  if (ema_here && !fresh0) {
-    m_run = exp(-2.0 * logq_decode(meta.z[t]));
-    e_run = 2.0 * (double)f16_to_f32(meta.r16[t]);
-  }
-  const bool erase = !p.no_erase;
-  int prev0 = 0, prevn = 0;
-  for (int j0 = 0; j0 < p.ntk; j0 += TS) {
-    const int nt = min(TS, p.ntk - j0);
-    __syncthreads();   // the previous batch's readers are done with the tables
-    if (prevn > 0) write_o(prev0, prevn);
-    stage(nt);
-    if (j0 + TS < p.ntk) issue(j0 + TS);
-    __syncthreads();
-    if (ema_here) {
-      // token-sequential EMA of row t (the first token initialises a fresh record)
-      for (int j = 0; j < nt; ++j) {
-        const double zs = ps.z[j][t];
-        const double ys = erase ? erase_sample(ps.rq[j][t].y, ps.beta[j]) : 0.0;
-        if (fresh0 && j0 + j == 0) {
-          m_run = zs;
-          e_run = ys;
-        } else {
-          m_run = p.one_minus_alpha * m_run + p.alpha * zs;
-          e_run = p.one_minus_alpha * e_run + p.alpha * ys;
-        }
+  // The two halves run separate loops (waves take one side or the other whole;
+  // both pass the same number of barriers), so that neither's registers are
+  // held by the other.
+  if (feeds) {
+    if (ema) {
+      fresh = meta.ntok == 0;
+      if (!fresh) {
+        m_run = exp(-2.0 * logq_decode(meta.z[fi]));
+        e_run = 2.0 * (double)f16_to_f32(meta.r16[fi]);
       }
     }
-    // rows 32 rb + lane % 16 and 32 rb + 16 + lane % 16: DPP broadcast sources.
-    // The batch's first token runs its first pass alone; every later token's
-    // first pass is fused with the previous token's second pass (fused_pass),
-    // and the batch's last token runs its second pass alone.
-    float4 s0 = ps.rq[0][rb * ROW_BLOCK + (lane & 15)];
-    float4 s1 = ps.rq[0][rb * ROW_BLOCK + 16 + (lane & 15)];
-    float accU = 0.f;
-    pass1_16<0, 0, 1>(X, accU, s0.x, s0.y);
-    pass1_16<16, 0, 1>(X, accU, s1.x, s1.y);
-    for (int j = 0; j + 1 < nt; ++j) {
-      const float vj = ps.v[j][col];
-      const float4 n0 = ps.rq[j + 1][rb * ROW_BLOCK + (lane & 15)];
-      const float4 n1 = ps.rq[j + 1][rb * ROW_BLOCK + 16 + (lane & 15)];
-      const float u = rowblock_sum<NRB>(accU);
-      const float wv = erase ? vj - u : vj;   // no erasure: w = v
-      float accO = 0.f;
-      accU = 0.f;
-      fused_pass(X, accO, accU, s0.z, s0.w, n0.x, n0.y, s1.z, s1.w, n1.x, n1.y, wv);
-      s0 = n0;
-      s1 = n1;
-      const float o = rowblock_sum<NRB>(accO);
-      if (rb == 0) ps.o[j][col] = o;
+    if (p.ntk > 0) stage(0, 0);
+    if (TS < p.ntk) issue(TS);
+    __syncthreads();
+    int buf = 0;
+    for (int j0 = 0; j0 < p.ntk; j0 += TS, buf ^= 1) {
+      if (j0 > 0) write_o(j0 - TS, buf ^ 1);
+      if (j0 + TS < p.ntk) {
+        stage(j0 + TS, buf ^ 1);
+        if (j0 + 2 * TS < p.ntk) issue(j0 + 2 * TS);
+      }
+      __syncthreads();
     }
-    {
-      const float vj = ps.v[nt - 1][col];
+    if (p.ntk > 0) write_o((p.ntk - 1) / TS * TS, buf ^ 1);
+    if (ema) {
+      const double s_hat = -0.5 * log(m_run);
+      const double r = 0.5 * e_run;
+      p.ws_gam[(size_t)bh * DK + fi] = p.gamma ? p.gamma[(size_t)bh * DK + fi] : mode_gamma(p.weight_mode, s_hat, r, p.wb_C);
+      p.ws_zr[(size_t)bh * DK + fi] = (uint32_t)logq_encode(s_hat) | ((uint32_t)r_encode(r) << 16);
+    }
+  } else {
+    const int rb = lane / CPW, col = w * CPW + lane % CPW;   // slice-local column
+    float X[ROW_BLOCK][1];
+    // decode rows 32 rb + r of this lane's column: descriptors per lane (the
+    // row blocks of a wave differ), x^ = (code + add) mul as in unpack_cols
+#pragma unroll
+    for (int r = 0; r < ROW_BLOCK; ++r) {
+      const uint4 d = meta.desc[rb * ROW_BLOCK + r];
+      const int sh = (int)(d.y & 31u), bw = (int)(d.y >> 8);
+      const uint32_t lo = words[d.x + col], hi = words[d.x + SLICE + col];
+      const int code = __builtin_amdgcn_sbfe((int)__builtin_amdgcn_alignbit(hi, lo, (uint32_t)sh), 0, bw);
+      X[r][0] = ((float)code + __builtin_bit_cast(float, d.w)) * __builtin_bit_cast(float, d.z);
+    }
+    __syncthreads();
+    int buf = 0;
+    for (int j0 = 0; j0 < p.ntk; j0 += TS, buf ^= 1) {
+      const int nt = min(TS, p.ntk - j0);
+      // rows 32 rb + lane % 16 and 32 rb + 16 + lane % 16: DPP broadcast sources.
+      // The batch's first token runs its first pass alone; every later token's
+      // first pass is fused with the previous token's second pass (fused_pass),
+      // and the batch's last token runs its second pass alone.  A token's row
+      // scalars are read a whole pass ahead of their use.
+      const float4(*rq)[DK] = ps.rq[buf];
+      const int r0 = rb * ROW_BLOCK + (lane & 15);
+      float4 s0 = rq[0][r0], s1 = rq[0][r0 + 16];
+      float4 n0 = rq[min(1, nt - 1)][r0], n1 = rq[min(1, nt - 1)][r0 + 16];
+      float vj = ps.v[buf][0][col];
+      float accU = 0.f;
+      pass1_16<0, 0, 1>(X, accU, s0.x, s0.y);
+      pass1_16<16, 0, 1>(X, accU, s1.x, s1.y);
+      for (int j = 0; j + 1 < nt; ++j) {
+        const int ja = min(j + 2, nt - 1);
+        const float4 a0 = rq[ja][r0], a1 = rq[ja][r0 + 16];
+        const float va = ps.v[buf][j + 1][col];
+        const float u = rowblock_sum<NRB>(accU);
+        const float wv = erase ? vj - u : vj;   // no erasure: w = v
+        float accO = 0.f;
+        accU = 0.f;
+        fused_pass(X, accO, accU, s0.z, s0.w, n0.x, n0.y, s1.z, s1.w, n1.x, n1.y, wv);
+        s0 = n0;
+        s1 = n1;
+        n0 = a0;
+        n1 = a1;
+        vj = va;
+        const float o = rowblock_sum<NRB>(accO);
+        if (rb == 0) ps.o[buf][j][col] = o;
+      }
       const float u = rowblock_sum<NRB>(accU);
       const float wv = erase ? vj - u : vj;
       float accO = 0.f;
       pass2_16<0, 0, 1>(X, accO, s0.z, s0.w, wv);
       pass2_16<16, 0, 1>(X, accO, s1.z, s1.w, wv);
       const float o = rowblock_sum<NRB>(accO);
-      if (rb == 0) ps.o[nt - 1][col] = o;
+      if (rb == 0) ps.o[buf][nt - 1][col] = o;
+      __syncthreads();
     }
-    prev0 = j0;
-    prevn = nt;
-  }
-  __syncthreads();
-  write_o(prev0, prevn);
-  {
     // float32 state after the chunk (this lane's column), row-major
     float* dstS = p.ws_s32 + (size_t)bh * DK * p.dv + sl * SLICE + col;
 #pragma unroll
     for (int r = 0; r < ROW_BLOCK; ++r) dstS[(size_t)(rb * ROW_BLOCK + r) * p.dv] = X[r][0];
-  }
-  // row maxima over the slice: the wave's columns, then the waves
+    // row maxima over the slice: the wave's columns, then the waves
 #pragma unroll
-  for (int r = 0; r < ROW_BLOCK; ++r) {
-    const float m = rowblock_max<CPW>(fabsf(X[r][0]));
-    if (lane % CPW == 0) ps.Rw[w][rb * ROW_BLOCK + r] = m;
+    for (int r = 0; r < ROW_BLOCK; ++r) {
+      const float m = rowblock_max<CPW>(fabsf(X[r][0]));
+      if (lane % CPW == 0) ps.Rw[w][rb * ROW_BLOCK + r] = m;
+    }
   }
   __syncthreads();
   if (t < DK) {
@@ -848,12 +883,6 @@ __global__ void __launch_bounds__(2 * DK) k_chunk_cols(KParams p) {
 #pragma unroll
     for (int q = 1; q < NRB; ++q) m = fmaxf(m, ps.Rw[q][t]);
     p.ws_rpart[((size_t)bh * DK + t) * nsl + sl] = m;
-  }
-  if (ema_here) {
-    const double s_hat = -0.5 * log(m_run);
-    const double r = 0.5 * e_run;
-    p.ws_gam[(size_t)bh * DK + t] = p.gamma ? p.gamma[(size_t)bh * DK + t] : mode_gamma(p.weight_mode, s_hat, r, p.wb_C);
-    p.ws_zr[(size_t)bh * DK + t] = (uint32_t)logq_encode(s_hat) | ((uint32_t)r_encode(r) << 16);
   }
 }
 
@@ -1052,11 +1081,9 @@ static hipError_t launch_interval_slices(const KParams& p, hipStream_t st) {
   const size_t dyn = (size_t)(p.L.wc + 1) * SLICE * 4;
   hipError_t e;
   if constexpr (DK <= 128)
-    e = p.in_bf16 ? launch("stats", k_chunk_cols<DK, true>, p.B * p.H * nsl, 2 * DK, dyn, st, p)
-                  : launch("stats", k_chunk_cols<DK, false>, p.B * p.H * nsl, 2 * DK, dyn, st, p);
+    e = launch("stats", k_chunk_cols<DK>, p.B * p.H * nsl, 4 * DK, dyn, st, p);
   else
-    e = p.in_bf16 ? launch("stats", k_chunk_slices<DK, true>, p.B * p.H * nsl, 2 * DK, dyn, st, p)
-                  : launch("stats", k_chunk_slices<DK, false>, p.B * p.H * nsl, 2 * DK, dyn, st, p);
+    e = launch("stats", k_chunk_slices<DK>, p.B * p.H * nsl, 2 * DK, dyn, st, p);
   if (e != hipSuccess) return e;
   return launch_chunk_writeback(p, nsl, st);
 }
