@@ -397,15 +397,23 @@ __global__ void __launch_bounds__(2 * DK) k_step32(KParams p) {
                                           BUF_NT);
 }
 
-// Standalone codec: quantise given states.
-template <int DK, int DV>
-__global__ void __launch_bounds__(2 * DK) k_pack(KParams p, const float* S, const uint8_t* bits,
-                                                 const double* s_hat, const double* r,
-                                                 unsigned ntok) {
-  const int bh = blockIdx.x;
+// Standalone codec: quantise given states.  As the write-back's fit: PAIRS
+// candidate lanes per row segment, PARTS blocks per head, the rows staged in
+// LDS (d_k <= 128) with coalesced reads while the width order is formed.
+template <int DK, bool C8, int PAIRS, int PARTS, bool STAGE>
+__global__ void __launch_bounds__(requant_threads(DK, DK, PAIRS, PARTS))
+    k_pack(KParams p, const float* S, const uint8_t* bits, const double* s_hat, const double* r, unsigned ntok) {
+  constexpr int DV = DK, ROWS = DK / PARTS, NTH = requant_threads(DK, DV, PAIRS, PARTS);
+  constexpr int NV = STAGE ? ROWS * DV / 4 / NTH : 1;
+  static_assert(!STAGE || (ROWS * DV / 4) % NTH == 0, "whole float4 per thread");
+  using CT = CodeTile<C8>;
+  int bh = blockIdx.x, part = 0;
+  if constexpr (PARTS > 1) slice_block(p.B * p.H, PARTS, bh, part);
+  const int r0 = part * ROWS;
   const Layout L = p.L;
   uint8_t* rec = (uint8_t*)p.records + L.slot * (long long)bh;
-  __shared__ __align__(16) CodeT<DK> Ct[DV * CT_LD_OF<DK>];
+  __shared__ __align__(16) float sx[STAGE ? ROWS * stage_row<DV>() : 4];
+  __shared__ __align__(16) CT Ct[DV * ct_ld<DK, CT>()];
   __shared__ __align__(16) uint8_t nb[DK];
   __shared__ uint8_t perm[DK];
   __shared__ uint16_t sc16[DK], zz[DK], rr[DK];
@@ -413,20 +421,28 @@ __global__ void __launch_bounds__(2 * DK) k_pack(KParams p, const float* S, cons
   __shared__ OrderSmem<DK> os;
   __shared__ uint32_t tail[DV];
   const int t = threadIdx.x;
+  const float* Sh = S + (size_t)bh * DK * DV;
+  v4f sv[NV];
+  if constexpr (STAGE) stage_request(Sh + (size_t)r0 * DV, sv, NTH);
   if (t < DK) {
     nb[t] = (uint8_t)min(max((int)bits[(size_t)bh * DK + t], 1), p.bmax);
-    zz[t] = logq_encode(s_hat[(size_t)bh * DK + t]);
-    rr[t] = r_encode(r[(size_t)bh * DK + t]);
+    if (t >= r0 && t < r0 + ROWS) {
+      zz[t] = logq_encode(s_hat[(size_t)bh * DK + t]);
+      rr[t] = r_encode(r[(size_t)bh * DK + t]);
+    }
   }
+  if constexpr (STAGE) stage_store<DV>(sx, sv, NTH);
   for (int e = t; e < (MAX_B + 1) * N_FIT; e += blockDim.x) phi[e / N_FIT][e % N_FIT] = p.phi[e / N_FIT][e % N_FIT];
   __syncthreads();
-  width_order<DK>(nb, perm, os);
-  const float* Sh = S + (size_t)bh * DK * DV;
-  fit_rows<DK, DV>([&](int i, int sg, float (&x)[SEG]) { load_dense<DV>(Sh, i, sg, x); }, nb, perm,
-                   phi, Ct, sc16, p.diag_fit);
+  width_order<DK>(nb, perm, os, r0, r0 + ROWS, p.bmax);
+  auto load = [&](int i, int sg, float (&x)[SEG]) {
+    if constexpr (STAGE) load_staged<DV>(sx, min(max(i - r0, 0), ROWS - 1), sg, x);
+    else load_dense<DV>(Sh, i, sg, x);
+  };
+  fit_rows<DK, DV, false, PAIRS, ROWS>(load, nb, perm, phi, Ct, sc16, p.diag_fit);
   __syncthreads();
-  pack_cols<DK, DV>(Ct, nb, os.P, (uint32_t*)(rec + L.codes_off), tail);
-  store_meta<DK>(rec, L, ntok, nb, sc16, zz, rr);
+  pack_cols<DK, DV, ROWS>(Ct, nb, os.P, (uint32_t*)(rec + L.codes_off), tail, r0);
+  store_meta<DK, ROWS>(rec, L, ntok, nb, sc16, zz, rr, r0);
 }
 
 // Standalone codec: decode records.
@@ -1056,8 +1072,12 @@ static hipError_t launch_interval_t(const KParams& p, hipStream_t st, int phases
     return launch("requant", k_requant<DK, DV, false, true>, nbh, 2 * DK, 0, st, p);
   } else {
     if (wb == WB_QUAD) return launch_chunk_requant(p, st);
-    return c8 ? launch("requant", k_requant<DK, DV, true, true>, nbh, 2 * DK, 0, st, p)
-              : launch("requant", k_requant<DK, DV, true, false>, nbh, 2 * DK, 0, st, p);
+    // d_k = 64: a wave of one lane per row would hold a whole head and pay the
+    // longest scan of any of its rows; two lanes per row (2048 heads: 53 -> 44 us
+    // a step, 4096: 88 -> 70; at 128 two lanes are slower from 768 heads on)
+    constexpr int PR = DK == 64 ? 2 : 1, NTH = requant_threads(DK, DV, PR);
+    return c8 ? launch("requant", k_requant<DK, DV, true, true, PR>, nbh, NTH, 0, st, p)
+              : launch("requant", k_requant<DK, DV, true, false, PR>, nbh, NTH, 0, st, p);
   }
 }
 
@@ -1132,13 +1152,37 @@ hipError_t launch_prefill(KParams p, int C, hipStream_t st) {
   return hipSuccess;
 }
 
+template <int DK, int PAIRS, int PARTS, bool STAGE>
+static hipError_t launch_pack_t(const KParams& p, const float* S, const uint8_t* bits, const double* s_hat,
+                                const double* r, unsigned ntok, hipStream_t st) {
+  const int nblk = p.B * p.H * PARTS;
+  constexpr int NTH = requant_threads(DK, DK, PAIRS, PARTS);
+  return DK > 128 || p.bmax <= 8
+             ? launch("pack", k_pack<DK, true, PAIRS, PARTS, STAGE>, nblk, NTH, 0, st, p, S, bits, s_hat, r, ntok)
+             : launch("pack", k_pack<DK, (DK > 128), PAIRS, PARTS, STAGE>, nblk, NTH, 0, st, p, S, bits, s_hat, r, ntok);
+}
+
+// Lanes per row segment, blocks per head and staging by the number of heads
+// (us per call, one lane and block per head / two lanes, two blocks / four lanes,
+// two blocks, staged; d_k = 128, four bits):
+//   128 heads: 20.0 14.4 13.3   256: 20.7 19.1 18.4   512: 25.8 25.6 31.7
+//   768: 33.0 34.8 44.4   1024: 36.6 45.5 58.1
+// Few heads are bound by the latency of a block's scan, many by instructions,
+// and the staged rows' LDS (33 KB) then keeps blocks off the compute units.
+// d_k = 64 (a wave of single lanes holds all 64 rows, and pays the longest scan
+// of any; one lane / two / four, staged): 256 heads: 18.9 13.2 10.8, 1024: 24.6
+// 18.0 16.5, 2048: 36.9 26.1 29.1.  d_k = 256: a thread per row segment (1024)
+// instead of two segments in turn: 41.8 -> 36.7 at 256 heads.
 hipError_t launch_pack(const KParams& p, const float* S, const uint8_t* bits, const double* s_hat,
                        const double* r, unsigned ntok, hipStream_t st) {
   const int nbh = p.B * p.H;
-  if (p.dk == 64) return launch("pack", k_pack<64, 64>, nbh, 128, 0, st, p, S, bits, s_hat, r, ntok);
-  if (p.dk == 256)
-    return launch("pack", k_pack<256, 256>, nbh, 512, 0, st, p, S, bits, s_hat, r, ntok);
-  return launch("pack", k_pack<128, 128>, nbh, 256, 0, st, p, S, bits, s_hat, r, ntok);
+  if (p.dk == 64)
+    return nbh <= 1024 ? launch_pack_t<64, 4, 1, true>(p, S, bits, s_hat, r, ntok, st)
+                       : launch_pack_t<64, 2, 1, false>(p, S, bits, s_hat, r, ntok, st);
+  if (p.dk == 256) return launch_pack_t<256, 1, 1, false>(p, S, bits, s_hat, r, ntok, st);
+  if (nbh <= 256) return launch_pack_t<128, 4, 2, true>(p, S, bits, s_hat, r, ntok, st);
+  return nbh <= 640 ? launch_pack_t<128, 2, 2, false>(p, S, bits, s_hat, r, ntok, st)
+                    : launch_pack_t<128, 1, 1, false>(p, S, bits, s_hat, r, ntok, st);
 }
 
 hipError_t launch_unpack(const KParams& p, float* S, uint8_t* bits, double* s_hat, double* r,

@@ -19,15 +19,8 @@ namespace kda {
 
 // ----------------------------------------------------- row-layout fit ---
 
-// Codes in LDS: int16 (widths up to 16) for d_k <= 128, int8 for d_k = 256
-// (widths up to 8), so that the column-major code tile fits in LDS.
-template <int DK>
-using CodeT = typename std::conditional<(DK > 128), int8_t, int16_t>::type;
-
 // Column stride (elements) of the column-major code buffer: padded by 16 bytes
 // so that the 16-byte reads of consecutive columns hit distinct LDS banks.
-template <int DK>
-constexpr int CT_LD_OF = DK + 16 / (int)sizeof(CodeT<DK>);
 template <int DK, typename CT>
 constexpr int ct_ld() { return DK + 16 / (int)sizeof(CT); }
 
@@ -467,6 +460,39 @@ __device__ __forceinline__ void load_dense(const float* S, int i, int sg, float 
   }
 }
 
+// Rows of a float32 state in LDS: row r at r SROW, segment g of it SEG + 4
+// floats further per segment (the rows and segments of a wave's items fall in
+// different banks).  N float4 per thread, requested into registers first and
+// stored once the caller has other work in flight.
+template <int DV>
+constexpr int stage_row() { return DV + 4 * (DV / SEG); }
+typedef float v4f __attribute__((ext_vector_type(4)));   // held in registers, not copied through memory
+template <int N>
+__device__ __forceinline__ void stage_request(const float* S, v4f (&sv)[N], int nth) {
+#pragma unroll
+  for (int q = 0; q < N; ++q) sv[q] = ((const v4f*)S)[threadIdx.x + q * nth];
+}
+template <int DV, int N>
+__device__ __forceinline__ void stage_store(float* sx, const v4f (&sv)[N], int nth) {
+#pragma unroll
+  for (int q = 0; q < N; ++q) {
+    const int e = 4 * ((int)threadIdx.x + q * nth), r = e / DV, c = e % DV;
+    *(v4f*)&sx[r * stage_row<DV>() + c + 4 * (c / SEG)] = sv[q];
+  }
+}
+template <int DV>
+__device__ __forceinline__ void load_staged(const float* sx, int r, int sg, float (&x)[SEG]) {
+  const float4* src = (const float4*)&sx[r * stage_row<DV>() + sg * (SEG + 4)];
+#pragma unroll
+  for (int q = 0; q < SEG / 4; ++q) {
+    const float4 v = src[q];
+    x[4 * q] = v.x;
+    x[4 * q + 1] = v.y;
+    x[4 * q + 2] = v.z;
+    x[4 * q + 3] = v.w;
+  }
+}
+
 // What the requantisation of a decode step needs besides its own tables when
 // it rebuilds the state from the record: the record's decode metadata and the
 // token's column vector w.
@@ -526,21 +552,14 @@ __device__ __forceinline__ void requant_head(const KParams& p, int bh, RequantLd
   // The float32 rows of this block's part (not the decode step: it rebuilds
   // its rows), when they fit in LDS: requested first, so that their latency
   // passes during the allocation and the width order, and read by the fit
-  // from LDS.  Row r at sx[r SROW], segment g of it SEG + 4 floats further
-  // per segment (the rows and segments of a wave's items fall in different
-  // banks).
-  constexpr int SROW = DV + 4 * (DV / SEG), NTH = requant_threads(DK, DV, PAIRS, PARTS);
+  // from LDS.
+  constexpr int SROW = stage_row<DV>(), NTH = requant_threads(DK, DV, PAIRS, PARTS);
   constexpr bool STAGE = !COMPACT && (size_t)ROWS * SROW * 4 <= 40 * 1024;
   constexpr int NV = STAGE ? ROWS * DV / 4 / NTH : 1;
   static_assert(!STAGE || (ROWS * DV / 4) % NTH == 0, "whole float4 per thread");
-  typedef float v4f __attribute__((ext_vector_type(4)));   // held in registers, not copied through memory
   __shared__ __align__(16) float sx[STAGE ? ROWS * SROW : 4];
   v4f sv[NV];
-  if constexpr (STAGE) {
-    const v4f* S4 = (const v4f*)(p.ws_s32 + ((size_t)bh * DK + r0) * DV);
-#pragma unroll
-    for (int q = 0; q < NV; ++q) sv[q] = S4[t + q * NTH];
-  }
+  if constexpr (STAGE) stage_request(p.ws_s32 + ((size_t)bh * DK + r0) * DV, sv, NTH);
   const uint32_t zr = t < DK ? p.ws_zr[(size_t)bh * DK + t] : 0u;
   if constexpr (ALLOC) {
     static_assert(!COMPACT && sizeof(AllocSmem) <= sizeof(sm.Ct), "allocator scratch in the code tile");
@@ -558,13 +577,7 @@ __device__ __forceinline__ void requant_head(const KParams& p, int bh, RequantLd
     sm.zz[t] = (uint16_t)(zr & 0xffffu);
     sm.rr[t] = (uint16_t)(zr >> 16);
   }
-  if constexpr (STAGE) {
-#pragma unroll
-    for (int q = 0; q < NV; ++q) {
-      const int e = 4 * (t + q * NTH), r = e / DV, c = e % DV;
-      *(v4f*)&sx[r * SROW + c + 4 * (c / SEG)] = sv[q];
-    }
-  }
+  if constexpr (STAGE) stage_store<DV>(sx, sv, NTH);
   for (int e = t; e < (MAX_B + 1) * N_FIT; e += blockDim.x)
     sm.phi[e / N_FIT][e % N_FIT] = p.phi[e / N_FIT][e % N_FIT];
   if constexpr (COMPACT) {
@@ -616,22 +629,13 @@ __device__ __forceinline__ void requant_head(const KParams& p, int bh, RequantLd
         x[j] = __builtin_fmaf(gi, sm.rb.wv[sg * SEG + j], ai * xh);
       }
     };
-    fit_rows<DK, DV, true>(rebuild, sm.nb, sm.perm, sm.phi, sm.Ct, sm.sc16, p.diag_fit);
+    fit_rows<DK, DV, true, PAIRS>(rebuild, sm.nb, sm.perm, sm.phi, sm.Ct, sm.sc16, p.diag_fit);
   } else {
     __syncthreads();
     width_order<DK>(sm.nb, sm.perm, sm.os, r0, r0 + ROWS, p.bmax);
     const float* S = p.ws_s32 + (size_t)bh * DK * DV;
     auto staged = [&](int i, int sg, float (&x)[SEG]) {
-      const int li = min(max(i - r0, 0), ROWS - 1);
-      const float4* src = (const float4*)&sx[li * SROW + sg * (SEG + 4)];
-#pragma unroll
-      for (int q = 0; q < SEG / 4; ++q) {
-        const float4 v = src[q];
-        x[4 * q] = v.x;
-        x[4 * q + 1] = v.y;
-        x[4 * q + 2] = v.z;
-        x[4 * q + 3] = v.w;
-      }
+      load_staged<DV>(sx, min(max(i - r0, 0), ROWS - 1), sg, x);
     };
     auto dense = [&](int i, int sg, float (&x)[SEG]) { load_dense<DV>(S, i, sg, x); };
     if constexpr (STAGE)
@@ -667,7 +671,7 @@ constexpr int par_rows() { return DK == 64 ? 64 : 32; }   // rows per block
 template <int DK, typename CT>
 struct ParLds {
   static constexpr int ROWS = par_rows<DK>(), LD = ROWS + 16 / (int)sizeof(CT);
-  static constexpr int SROW = DK + 4 * (DK / SEG);
+  static constexpr int SROW = stage_row<DK>();
   union {
     AllocSmem al;
     __align__(16) CT Ct[DK * LD];   // codes, column-major, rows of the block
@@ -718,13 +722,8 @@ __device__ __forceinline__ void requant_par(const KParams& p, int bh, int part, 
   const Layout L = p.L;
   uint8_t* rec = (uint8_t*)slot_ptr(p.records, L.slot, bh);
   const unsigned ntok = *(const unsigned*)rec;
-  typedef float v4f __attribute__((ext_vector_type(4)));
   v4f sv[NV];
-  {
-    const v4f* S4 = (const v4f*)(p.ws_s32 + ((size_t)bh * DK + r0) * DV);
-#pragma unroll
-    for (int q = 0; q < NV; ++q) sv[q] = S4[t + q * NT];
-  }
+  stage_request(p.ws_s32 + ((size_t)bh * DK + r0) * DV, sv, NT);
   const uint32_t zr = t < DK ? p.ws_zr[(size_t)bh * DK + t] : 0u;
   if constexpr (ALLOC) {
     const int N = p.H * DK, unit = bh / p.H, row0 = (bh % p.H) * DK;
@@ -738,11 +737,7 @@ __device__ __forceinline__ void requant_par(const KParams& p, int bh, int part, 
     sm.zz[t] = (uint16_t)(zr & 0xffffu);
     sm.rr[t] = (uint16_t)(zr >> 16);
   }
-#pragma unroll
-  for (int q = 0; q < NV; ++q) {
-    const int e = 4 * (t + q * NT), r = e / DV, c = e % DV;
-    *(v4f*)&sm.sx[r * SROW + c + 4 * (c / SEG)] = sv[q];
-  }
+  stage_store<DV>(sm.sx, sv, NT);
   for (int e = t; e < (MAX_B + 1) * N_FIT; e += NT) sm.phi[e / N_FIT][e % N_FIT] = p.phi[e / N_FIT][e % N_FIT];
   // bit offsets of the rows: wave totals now, the sums over waves below
   int incl = 0;
@@ -762,14 +757,7 @@ __device__ __forceinline__ void requant_par(const KParams& p, int bh, int part, 
     const int lr = item / SEGS, sg = item % SEGS, i = r0 + lr;
     const float* xs = &sm.sx[lr * SROW + sg * (SEG + 4)];
     float x[SEG];
-#pragma unroll
-    for (int u = 0; u < SEG / 4; ++u) {
-      const float4 v = ((const float4*)xs)[u];
-      x[4 * u] = v.x;
-      x[4 * u + 1] = v.y;
-      x[4 * u + 2] = v.z;
-      x[4 * u + 3] = v.w;
-    }
+    load_staged<DV>(sm.sx, lr, sg, x);
     const int b = sm.nb[i];
     const float4 xq = ((const float4*)xs)[q];   // the four columns this lane codes
     const float xw[4] = {xq.x, xq.y, xq.z, xq.w};
