@@ -896,24 +896,38 @@ __global__ void __launch_bounds__(256) k_chunk_rates(KParams p, int C, uint8_t* 
   } else {
     zr = carry[gi];
   }
+  // A chunk's sums are requested a chunk ahead, and the power of the whole
+  // chunks' length is formed once: the chain of a chunk is then its
+  // transcendentals alone (16 chunks of 4096 rows: 38 -> 21 us)
+  auto sums = [&](int c) { return (const double*)(cws + ((size_t)c * nbh + bh) * CW::bytes + CW::ema); };
+  auto power = [&](int n) {
+    double P = 1.0;
+    for (int j = 0; j < n; ++j) P *= p.one_minus_alpha;
+    return P;
+  };
+  const double PC = power(C);   // C <= 64
+  double qm = sums(0)[t], qe = sums(0)[DK + t];
   for (int c = 0; c < nc; ++c) {
     const int k = first_chunk + c;
     const int n = (p.T - k * C) < C ? (p.T - k * C) : C;
     uint8_t* out = cws + ((size_t)c * nbh + bh) * CW::bytes;
-    const double* ema = (const double*)(out + CW::ema);
+    const double qm0 = qm, qe0 = qe;
+    if (c + 1 < nc) {
+      qm = sums(c + 1)[t];
+      qe = sums(c + 1)[DK + t];
+    }
     double m0, e0;
     if (fresh) {
-      m0 = ema[2 * DK + t];
-      e0 = ema[3 * DK + t];
+      m0 = sums(c)[2 * DK + t];
+      e0 = sums(c)[3 * DK + t];
       fresh = false;
     } else {
       m0 = exp(-2.0 * logq_decode((uint16_t)(zr & 0xffffu)));
       e0 = 2.0 * (double)f16_to_f32((uint16_t)(zr >> 16));
     }
-    double P = 1.0;
-    for (int j = 0; j < n; ++j) P *= p.one_minus_alpha;
-    const double m_run = P * m0 + ema[t];
-    const double e_run = P * e0 + ema[DK + t];
+    const double P = n == C ? PC : power(n);
+    const double m_run = P * m0 + qm0;
+    const double e_run = P * e0 + qe0;
     const double s_hat = -0.5 * log(m_run);
     const double r = 0.5 * e_run;
     ((double*)(out + CW::gam))[t] =
