@@ -985,6 +985,14 @@ static hipError_t launch_chunk_requant(const KParams& p, hipStream_t st) {
             : launch("requant", k_requant<128, 128, false, false, FL, PT>, nblk, T128, 0, st, p);
 }
 
+template <int DK, bool ALLOC>
+static hipError_t launch_requant_par(const KParams& p, hipStream_t st) {
+  const int nblk = p.B * p.H * (DK / par_rows<DK>());
+  return DK > 128 || p.bmax <= 8
+             ? launch("requant", k_requant_par<DK, true, ALLOC>, nblk, 1024, 0, st, p)
+             : launch("requant", k_requant_par<DK, (DK > 128), ALLOC>, nblk, 1024, 0, st, p);
+}
+
 // How a decode step is written back, by the size of the grid.  A block that
 // takes a whole head and scans the clip factors in turn (k_requant on the
 // rebuilt state) needs 20 us for one round of blocks, nearly all of it latency;
@@ -1061,13 +1069,7 @@ static hipError_t launch_interval_t(const KParams& p, hipStream_t st, int phases
   }
   if (!(phases & 2)) return hipSuccess;
   const bool c8 = DK > 128 || p.bmax <= 8;
-  if (wb == WB_PAR) {
-    if (alloc_in)
-      return c8 ? launch("requant", k_requant_par<DK, true, true>, par_blocks, 1024, 0, st, p)
-                : launch("requant", k_requant_par<DK, (DK > 128), true>, par_blocks, 1024, 0, st, p);
-    return c8 ? launch("requant", k_requant_par<DK, true, false>, par_blocks, 1024, 0, st, p)
-              : launch("requant", k_requant_par<DK, (DK > 128), false>, par_blocks, 1024, 0, st, p);
-  }
+  if (wb == WB_PAR) return alloc_in ? launch_requant_par<DK, true>(p, st) : launch_requant_par<DK, false>(p, st);
   if constexpr (DK > 128) {
     return launch("requant", k_requant<DK, DV, false, true>, nbh, 2 * DK, 0, st, p);
   } else {
@@ -1117,8 +1119,16 @@ static hipError_t launch_chunk_alloc(const KParams& p, int nsl, hipStream_t st, 
                 (const float*)p.ws_rpart, (const double*)p.ws_gam, p.ws_bits);
 }
 
-hipError_t launch_chunk_writeback(const KParams& p, int nsl, hipStream_t st, bool keys) {
-  if (keys && p.dk == 128) {
+template <int DK>
+static hipError_t chunk_writeback(const KParams& p, int nsl, hipStream_t st, bool keys) {
+  // few heads (blocks within one per compute unit): one lane per clip factor,
+  // with the selection of the widths when the keys are ready and the unit is a
+  // sequence.  B = 1, H = 32, d = 128: 12.4 us per chunked interval instead of
+  // the 18.3 of four lanes and two blocks per head; a second round of blocks
+  // would cost as much again
+  const bool par = p.B * p.H * (DK / par_rows<DK>()) <= 256;
+  if (par && keys && p.scope == 0) return launch_requant_par<DK, true>(p, st);
+  if (keys && DK == 128 && !par) {
     // the weights are ready: each requantisation block selects its unit's
     // widths itself (one launch per interval fewer)
     constexpr int FL = 4, PT = 2, T128 = requant_threads(128, 128, FL, PT);
@@ -1128,7 +1138,14 @@ hipError_t launch_chunk_writeback(const KParams& p, int nsl, hipStream_t st, boo
                : launch("requant", k_requant<128, 128, false, false, FL, PT, true>, nblk, T128, 0, st, p);
   }
   const hipError_t e = launch_chunk_alloc(p, nsl, st, keys);
-  return e != hipSuccess ? e : launch_chunk_requant(p, st);
+  if (e != hipSuccess) return e;
+  return par ? launch_requant_par<DK, false>(p, st) : launch_chunk_requant(p, st);
+}
+
+hipError_t launch_chunk_writeback(const KParams& p, int nsl, hipStream_t st, bool keys) {
+  if (p.dk == 64) return chunk_writeback<64>(p, nsl, st, keys);
+  if (p.dk == 256) return chunk_writeback<256>(p, nsl, st, keys);
+  return chunk_writeback<128>(p, nsl, st, keys);
 }
 
 hipError_t launch_prefill(KParams p, int C, hipStream_t st) {
