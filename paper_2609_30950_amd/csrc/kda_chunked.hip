@@ -62,11 +62,13 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));   // 16-byte copies held in registers
 
-// float -> bf16 bits, round to nearest even (finite inputs)
-__device__ __forceinline__ uint16_t bf16_rne(float x) {
-  uint32_t u = __builtin_bit_cast(uint32_t, x);
-  u += 0x7FFFu + ((u >> 16) & 1u);
-  return (uint16_t)(u >> 16);
+// float -> bf16 bits, round to nearest even (v_cvt_pk_bf16_f32: one
+// instruction where the integer form takes four).
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint16_t bf16_rne(float x) { return __builtin_bit_cast(uint16_t, (__bf16)x); }
+__device__ __forceinline__ uint32_t bf16_rne2(float a, float b) {
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){a, b}, bf16x2));
 }
 
 __device__ __forceinline__ float bf16_f32(uint16_t h) {
@@ -79,9 +81,8 @@ __device__ __forceinline__ uint16_t bf16_lo(float x, uint16_t hi) { return bf16_
 
 // Two values as packed hi and lo pairs.
 __device__ __forceinline__ void split2(float a, float b, uint32_t& hi, uint32_t& lo) {
-  const uint16_t ah = bf16_rne(a), bh = bf16_rne(b);
-  hi = (uint32_t)ah | ((uint32_t)bh << 16);
-  lo = (uint32_t)bf16_lo(a, ah) | ((uint32_t)bf16_lo(b, bh) << 16);
+  hi = bf16_rne2(a, b);
+  lo = bf16_rne2(a - __builtin_bit_cast(float, hi << 16), b - __builtin_bit_cast(float, hi & 0xFFFF0000u));
 }
 
 // D += A B for 16x16 tiles, K = 32: lane l supplies row l % 16 of A and
@@ -542,8 +543,8 @@ template <int DK>
 struct ApplySmem {
   static constexpr int SS = DK + 8;
   static constexpr int US = CT + 8;
-  uint16_t s0t[2][SLICE][SS];   // S0 of the slice, transposed, bf16 hi and lo planes
-  uint16_t ut[2][SLICE][US];    // U of the slice, transposed, bf16 hi and lo planes
+  __align__(16) uint16_t s0t[2][SLICE][SS];   // S0 of the slice, transposed, bf16 hi and lo planes
+  __align__(16) uint16_t ut[2][SLICE][US];    // U of the slice, transposed, bf16 hi and lo planes
 };
 
 // The chunk record's operands one wave of the apply holds in registers:
@@ -633,17 +634,16 @@ __device__ __forceinline__ void apply_slice(const KParams& p, const uint8_t* in,
   // so that it is not held through the first products)
 #pragma unroll
   for (int rt = 0; rt < RT; ++rt) {
+    const int i = 16 * (RT * w + rt) + 4 * (lane >> 4);
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int i = 16 * (RT * w + rt) + 4 * (lane >> 4) + r;
-#pragma unroll
-      for (int ct = 0; ct < 4; ++ct) {
-        const int c = 16 * ct + l16;
-        const float x = s0(i, c);
-        const uint16_t xh = bf16_rne(x);
-        sm.s0t[0][c][i] = xh;
-        sm.s0t[1][c][i] = bf16_lo(x, xh);
-      }
+    for (int ct = 0; ct < 4; ++ct) {
+      const int c = 16 * ct + l16;
+      // four rows of a column: one 8-byte store per plane
+      uint32_t h0, l0, h1, l1;
+      split2(s0(i, c), s0(i + 1, c), h0, l0);
+      split2(s0(i + 2, c), s0(i + 3, c), h1, l1);
+      *(uint2*)&sm.s0t[0][c][i] = make_uint2(h0, h1);
+      *(uint2*)&sm.s0t[1][c][i] = make_uint2(l0, l1);
     }
   }
   __syncthreads();
@@ -668,14 +668,12 @@ __device__ __forceinline__ void apply_slice(const KParams& p, const uint8_t* in,
   // U = Uv - W, transposed into LDS as hi and lo planes
 #pragma unroll
   for (int ct = 0; ct < 4; ++ct) {
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int j = 16 * w + 4 * (lane >> 4) + r, c = 16 * ct + l16;
-      const float u = f.fu[ct][r] - aw[ct][r];
-      const uint16_t uh = bf16_rne(u);
-      sm.ut[0][c][j] = uh;
-      sm.ut[1][c][j] = bf16_lo(u, uh);
-    }
+    const int j = 16 * w + 4 * (lane >> 4), c = 16 * ct + l16;
+    uint32_t h0, l0, h1, l1;
+    split2(f.fu[ct][0] - aw[ct][0], f.fu[ct][1] - aw[ct][1], h0, l0);
+    split2(f.fu[ct][2] - aw[ct][2], f.fu[ct][3] - aw[ct][3], h1, l1);
+    *(uint2*)&sm.ut[0][c][j] = make_uint2(h0, h1);
+    *(uint2*)&sm.ut[1][c][j] = make_uint2(l0, l1);
   }
   __syncthreads();
 
