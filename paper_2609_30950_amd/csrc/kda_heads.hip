@@ -160,10 +160,14 @@ __device__ __forceinline__ int fit_pack_block(const float (&X)[ROW_BLOCK][CPL], 
   uint32_t wd[B + 1];
 #pragma unroll
   for (int k = 0; k <= B; ++k) wd[k] = 0u;
+  // c = clamp(rint(fl32(x inv)), -n, n) as the low bits of M + c, M = 1.5 2^23
+  // (adding M rounds to an integer, ties to even, as rint does; larger
+  // magnitudes clamp to the same code): no rounding, conversion or sign mask
+  constexpr float M = 12582912.0f;
 #pragma unroll
   for (int r = 0; r < ROW_BLOCK; ++r) {
-    const int q = (int)__builtin_amdgcn_fmed3f(__builtin_rintf(X[r][c] * inv), -nf, nf);
-    const uint32_t field = (uint32_t)q & ((1u << B) - 1u);
+    const float q = __builtin_amdgcn_fmed3f(X[r][c] * inv + M, M - nf, M + nf);
+    const uint32_t field = __builtin_bit_cast(uint32_t, q) & ((1u << B) - 1u);
     const int pos = r * B, k = pos >> 5, sh = pos & 31;
     wd[k] |= field << sh;
     if (sh + B > 32) wd[k + 1] |= field >> (32 - sh);
