@@ -67,10 +67,15 @@ __device__ __forceinline__ void width_order(const uint8_t* bits, uint8_t* perm, 
   }
   __syncthreads();
   if (bp > 0) {
+    // every count is read (uniform addresses, all in flight), then selected
     int pos = below;
-    for (int v = bp + 1; v <= vmax; ++v)
-      for (int q = 0; q < DK / WAVE; ++q) pos += os.cnt[q][v];
-    for (int q = 0; q < w; ++q) pos += os.cnt[q][bp];
+#pragma unroll 8
+    for (int v = 1; v <= vmax; ++v)
+#pragma unroll
+      for (int q = 0; q < DK / WAVE; ++q) {
+        const int n = os.cnt[q][v];
+        pos += v > bp || (v == bp && q < w) ? n : 0;
+      }
     perm[pos] = (uint8_t)t;
   }
   // wave totals of widths -> global prefix
