@@ -439,7 +439,12 @@ __global__ void __launch_bounds__(requant_threads(DK, DK, PAIRS, PARTS))
     if constexpr (STAGE) load_staged<DV>(sx, min(max(i - r0, 0), ROWS - 1), sg, x);
     else load_dense<DV>(Sh, i, sg, x);
   };
-  fit_rows<DK, DV, false, PAIRS, ROWS>(load, nb, perm, phi, Ct, sc16, p.diag_fit);
+  if constexpr (STAGE && PAIRS > 1)
+    fit_rows<DK, DV, false, PAIRS, ROWS>(load, nb, perm, phi, Ct, sc16, p.diag_fit, [&](int i, int sg, int k) {
+      return load_staged_quad<DV>(sx, min(max(i - r0, 0), ROWS - 1), sg, k);
+    });
+  else
+    fit_rows<DK, DV, false, PAIRS, ROWS>(load, nb, perm, phi, Ct, sc16, p.diag_fit);
   __syncthreads();
   pack_cols<DK, DV, ROWS>(Ct, nb, os.P, (uint32_t*)(rec + L.codes_off), tail, r0);
   store_meta<DK, ROWS>(rec, L, ntok, nb, sc16, zz, rr, r0);

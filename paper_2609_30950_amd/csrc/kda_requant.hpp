@@ -166,11 +166,17 @@ __device__ __forceinline__ float ternary_code(float x, float K, float nKth) {
 // passes over it and the scan ends after the step: the same choice, at most
 // PAIRS - 1 evaluations more per row.
 // ROWS: the rows perm[0 .. ROWS) (a block may take part of a head's rows).
+// QUADS: load_quad(i, sg, k) returns columns 4 k .. 4 k + 3 of a segment again
+// (cheap: from LDS), and the candidate lanes of a segment share its codes,
+// every PAIRS-th group of four columns each, instead of the first lane writing
+// all 64 with the others idle.
+struct NoQuads {};
 template <int DK, int DV, bool SYNC_AFTER_LOAD = false, int PAIRS = 1, int ROWS = DK,
-          typename LoadRow, typename CT>
+          typename LoadRow, typename CT, typename LoadQuad = NoQuads>
 __device__ __forceinline__ void fit_rows(LoadRow load_row, const uint8_t* bits, const uint8_t* perm,
                          const float (*phi)[N_FIT], CT* Ct, uint16_t* scale_out,
-                         unsigned long long* diag) {
+                         unsigned long long* diag, LoadQuad load_quad = {}) {
+  constexpr bool QUADS = !std::is_same<LoadQuad, NoQuads>::value;
   constexpr int LD = ct_ld<DK, CT>();
   constexpr int SEGS = DV / SEG;
   constexpr int ITEMS = ROWS * SEGS * PAIRS;
@@ -210,11 +216,22 @@ __device__ __forceinline__ void fit_rows(LoadRow load_row, const uint8_t* bits, 
     // halving over segments: lanes differing in the top segment bit first
     acc = seg_combine_p<SEGS, PAIRS>(acc);
     const uint16_t mu = f32_to_f16_sat(acc * (1.0f / (float)DV));
-    if (writer) {
+    if constexpr (QUADS) {
+      if (valid) {
+#pragma unroll
+        for (int k = 0; k < SEG / 4 / PAIRS; ++k) {
+          const int c4 = k * PAIRS + half;
+          const float4 v = load_quad(i, sg, c4);
+          const float xv[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+          for (int e = 0; e < 4; ++e) dst[(size_t)(4 * c4 + e) * LD] = (CT)(xv[e] < 0.f ? 1 : 0);
+        }
+      }
+    } else if (writer) {
 #pragma unroll
       for (int j = 0; j < SEG; ++j) dst[(size_t)j * LD] = (CT)(x[j] < 0.f ? 1 : 0);
-      if (sg == 0) scale_out[i] = mu;
     }
+    if (writer && sg == 0) scale_out[i] = mu;
   } else {
     const float nf = (float)((1 << (b - 1)) - 1);
     float best = __builtin_inff();
@@ -308,21 +325,32 @@ __device__ __forceinline__ void fit_rows(LoadRow load_row, const uint8_t* bits, 
     const uint16_t dh = f32_to_f16_sat_nonneg(mx * phi[b][mb]);
     const float d = f16_to_f32(dh);
     const float inv = recip_f16_value(d);
-    if (writer) {
-      // c = clamp(rint(fl32(x inv)), -n, n) as M + c, M = 1.5 2^23: adding M
-      // to fl32(x inv) rounds it to an integer, ties to even, exactly as rint
-      // does while |x inv| < 2^22 (larger magnitudes clamp to the same code),
-      // and the low bits of M + c (a float in [2^23, 2^24)) are c in two's
-      // complement, which the truncating store keeps
-      constexpr float M = 12582912.0f;
-      const float lo = M - nf, hi = M + nf;
+    // c = clamp(rint(fl32(x inv)), -n, n) as M + c, M = 1.5 2^23: adding M
+    // to fl32(x inv) rounds it to an integer, ties to even, exactly as rint
+    // does while |x inv| < 2^22 (larger magnitudes clamp to the same code),
+    // and the low bits of M + c (a float in [2^23, 2^24)) are c in two's
+    // complement, which the truncating store keeps
+    constexpr float M = 12582912.0f;
+    const float lo = M - nf, hi = M + nf;
+    auto code = [&](float v) {
+      return (CT)__builtin_bit_cast(uint32_t, __builtin_amdgcn_fmed3f(v * inv + M, lo, hi));
+    };
+    if constexpr (QUADS) {
+      if (valid) {
 #pragma unroll
-      for (int j = 0; j < SEG; ++j) {
-        const float c = __builtin_amdgcn_fmed3f(x[j] * inv + M, lo, hi);
-        dst[(size_t)j * LD] = (CT)__builtin_bit_cast(uint32_t, c);
+        for (int k = 0; k < SEG / 4 / PAIRS; ++k) {
+          const int c4 = k * PAIRS + half;
+          const float4 v = load_quad(i, sg, c4);
+          const float xv[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+          for (int e = 0; e < 4; ++e) dst[(size_t)(4 * c4 + e) * LD] = code(xv[e]);
+        }
       }
-      if (sg == 0) scale_out[i] = dh;
+    } else if (writer) {
+#pragma unroll
+      for (int j = 0; j < SEG; ++j) dst[(size_t)j * LD] = code(x[j]);
     }
+    if (writer && sg == 0) scale_out[i] = dh;
   }
   if (diag != nullptr) {
     // all lanes have reconverged here
@@ -498,6 +526,11 @@ __device__ __forceinline__ void load_staged(const float* sx, int r, int sg, floa
   }
 }
 
+template <int DV>
+__device__ __forceinline__ float4 load_staged_quad(const float* sx, int r, int sg, int k) {
+  return ((const float4*)&sx[r * stage_row<DV>() + sg * (SEG + 4)])[k];
+}
+
 // What the requantisation of a decode step needs besides its own tables when
 // it rebuilds the state from the record: the record's decode metadata and the
 // token's column vector w.
@@ -643,7 +676,12 @@ __device__ __forceinline__ void requant_head(const KParams& p, int bh, RequantLd
       load_staged<DV>(sx, min(max(i - r0, 0), ROWS - 1), sg, x);
     };
     auto dense = [&](int i, int sg, float (&x)[SEG]) { load_dense<DV>(S, i, sg, x); };
-    if constexpr (STAGE)
+    auto quad = [&](int i, int sg, int k) {
+      return load_staged_quad<DV>(sx, min(max(i - r0, 0), ROWS - 1), sg, k);
+    };
+    if constexpr (STAGE && PAIRS > 1)
+      fit_rows<DK, DV, false, PAIRS, ROWS>(staged, sm.nb, sm.perm, sm.phi, sm.Ct, sm.sc16, p.diag_fit, quad);
+    else if constexpr (STAGE)
       fit_rows<DK, DV, false, PAIRS, ROWS>(staged, sm.nb, sm.perm, sm.phi, sm.Ct, sm.sc16, p.diag_fit);
     else
       fit_rows<DK, DV, false, PAIRS, ROWS>(dense, sm.nb, sm.perm, sm.phi, sm.Ct, sm.sc16, p.diag_fit);
