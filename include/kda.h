@@ -38,9 +38,10 @@
  *   allocations are); misaligned pointers give KDA_ERR_ARG.
  * - Workspace: kda_workspace_bytes() bytes, used as scratch by one call at a
  *   time (per-row weights, widths, rate codes, and between the passes of a
- *   write-back either the token's vectors a, g, w (decode, d_k <= 128: the
- *   requantisation rebuilds the state from the record) or the float32 state
- *   (prefill, d_k = 256)).  Concurrent calls must not share one.
+ *   write-back the token's vectors a, g, w (decode, d_k <= 128: the
+ *   requantisation of many heads rebuilds the state from the record with
+ *   them), the float32 state (prefill, d_k = 256), or both (decode of few
+ *   heads)).  Concurrent calls must not share one.
  */
 #ifndef KDA_H_
 #define KDA_H_
@@ -261,12 +262,13 @@ size_t kda_step_noalloc_max_bytes(void);
  * phase is Sec. 2, eq. rule and the rate statistics, weights and widths of
  * Sec. 3 (eq. weight, eq. alloc); the second is Sec. 3, Levels and storage.
  * kda_step_outputs: the token's recurrence, outputs o, rate statistics,
- *   weights and widths; what the write-back needs of the state after the
- *   token is left in ws (the token's vectors for d_k <= 128, else the float32
- *   state).  Records are only read.  Arguments as kda_step.
+ *   weights and widths (few heads: the weights; the write-back selects the
+ *   widths); what the write-back needs of the state after the token is left in
+ *   ws (the token's vectors for d_k <= 128, the float32 state for d_k = 256 and
+ *   for few heads).  Records are only read.  Arguments as kda_step.
  * kda_step_writeback: quantise the state after the token (rebuilt from the
- *   unchanged records and ws) with those widths and rewrite the records in
- *   place.  Must follow kda_step_outputs of the same records and ws (stream
+ *   unchanged records and ws, or left in ws) with the widths of those weights
+ *   and rewrite the records in place.  Must follow kda_step_outputs of the same records and ws (stream
  *   order or an event), before ws or the records are used by another call.  Not available in 32-bit mode (kda_step_outputs
  *   then does the whole step and kda_step_writeback returns KDA_OK).
  * kda_step(...) is kda_step_outputs(...) then kda_step_writeback(...) on one

@@ -434,7 +434,7 @@ __global__ void __launch_bounds__(requant_threads(DK, DK, PAIRS, PARTS))
   if constexpr (STAGE) stage_store<DV>(sx, sv, NTH);
   for (int e = t; e < (MAX_B + 1) * N_FIT; e += blockDim.x) phi[e / N_FIT][e % N_FIT] = p.phi[e / N_FIT][e % N_FIT];
   __syncthreads();
-  width_order<DK>(nb, perm, os, r0, r0 + ROWS, p.bmax);
+  width_order<DK, (PAIRS > 1)>(nb, perm, os, r0, r0 + ROWS, p.bmax);
   auto load = [&](int i, int sg, float (&x)[SEG]) {
     if constexpr (STAGE) load_staged<DV>(sx, min(max(i - r0, 0), ROWS - 1), sg, x);
     else load_dense<DV>(Sh, i, sg, x);
@@ -1007,16 +1007,19 @@ static hipError_t launch_requant_par(const KParams& p, hipStream_t st) {
 //    further round costs as much again.  d_k = 256: up to three rounds, with a
 //    separate allocation from the second on, since there a head takes 46 us.
 //  * WB_QUAD (d_k <= 128): four lanes per factor group and two blocks per head
-//    (as the prefill) up to a float32 state of 16 MB: 13 us at 64 to 256 heads
-//    of 128; from the next head on the compact form is the faster one.
+//    (as the prefill) up to 256 heads of 128 (12 us at 64 to 256) and 1024 of
+//    64; from there on the compact form is the faster one (384 heads: by the
+//    mix of widths; with none of two bits and no erasure 46.5 against 48.3).
 //  * WB_COMPACT / WB_HEAD: a block per head, the state rebuilt from the record
 //    (d_k <= 128) or read (256).
 // Whole steps, us, at a four-bit mean, COMPACT/HEAD, QUAD, PAR:
 //   d 128, heads 32: 36.6 28.4 22.3   64: 36.6 28.6 22.7   96: 36.7 29.1 32.8
-//          128: 36.9 29.4 33.2   256: 37.0 36.0 54.8   288: 43.6 43.8 66.3
+//          128: 36.9 29.4 33.2   256: 37.0 35.5 54.8   288: 43.6 42.2 66.3
+//          384: 44.1 43.5 77.3   512: 44.7 49.9 98.3
 //   d  64, heads 32: 35.2 23.4 19.2   256: 34.0 27.2 21.6   384: 38.5 28.0 30.8
-//          1024: 39.9 33.7 51.7   2048: 52.9 52.7 93.1
-//   d 256, heads 32: 58.5 - 31.7   64: 60.6 - 43.8   96: 62.6 - 53.8   128: 64.5 - 65.1
+//          1024: 33.9 33.4 51.7   1280: 38.9 39.8   2048: 43.8 51.0 93.1
+//          (COMPACT with two lanes per row from 1024 on)
+//   d 256, heads 32: 58.5 - 31.7   64: 60.6 - 43.8   96: 62.6 - 53.8   128: 59.1 - 65.1
 enum WriteBack { WB_COMPACT, WB_HEAD, WB_QUAD, WB_PAR };
 template <int DK>
 static WriteBack step_writeback(const KParams& p) {
@@ -1025,7 +1028,7 @@ static WriteBack step_writeback(const KParams& p) {
   const int par_blocks = nbh * (DK / par_rows<DK>());
   if (par_blocks <= 256 * (DK == 256 ? 3 : 1)) return WB_PAR;
   if (DK == 256) return WB_HEAD;
-  return (long long)nbh * DK * DK <= (4 << 20) ? WB_QUAD : WB_COMPACT;
+  return nbh <= (DK == 64 ? 1024 : 256) ? WB_QUAD : WB_COMPACT;
 }
 
 // The statistics pass of a decode step.

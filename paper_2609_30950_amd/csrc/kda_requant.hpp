@@ -47,7 +47,9 @@ struct OrderSmem {
 // perm[0 .. hi - lo) lists the rows lo .. hi - 1 by width, widest first
 // (ties in row order); os.P holds the bit offsets of all DK rows.  vmax: the
 // largest width any row may have (the counts above it are not formed).
-template <int DK>
+// AHEAD: the counts are all read before any is used (latency-bound blocks);
+// else only those of wider rows, in turn, with fewer registers.
+template <int DK, bool AHEAD = false>
 __device__ __forceinline__ void width_order(const uint8_t* bits, uint8_t* perm, OrderSmem<DK>& os,
                                             int lo = 0, int hi = DK, int vmax = MAX_B) {
   const int t = threadIdx.x, w = t / WAVE, lane = lane_id();
@@ -67,15 +69,20 @@ __device__ __forceinline__ void width_order(const uint8_t* bits, uint8_t* perm, 
   }
   __syncthreads();
   if (bp > 0) {
-    // every count is read (uniform addresses, all in flight), then selected
     int pos = below;
+    if constexpr (AHEAD) {
 #pragma unroll 8
-    for (int v = 1; v <= vmax; ++v)
+      for (int v = 1; v <= vmax; ++v)
 #pragma unroll
-      for (int q = 0; q < DK / WAVE; ++q) {
-        const int n = os.cnt[q][v];
-        pos += v > bp || (v == bp && q < w) ? n : 0;
-      }
+        for (int q = 0; q < DK / WAVE; ++q) {
+          const int n = os.cnt[q][v];
+          pos += v > bp || (v == bp && q < w) ? n : 0;
+        }
+    } else {
+      for (int v = bp + 1; v <= vmax; ++v)
+        for (int q = 0; q < DK / WAVE; ++q) pos += os.cnt[q][v];
+      for (int q = 0; q < w; ++q) pos += os.cnt[q][bp];
+    }
     perm[pos] = (uint8_t)t;
   }
   // wave totals of widths -> global prefix
@@ -227,11 +234,12 @@ __device__ __forceinline__ void fit_rows(LoadRow load_row, const uint8_t* bits, 
           for (int e = 0; e < 4; ++e) dst[(size_t)(4 * c4 + e) * LD] = (CT)(xv[e] < 0.f ? 1 : 0);
         }
       }
+      if (writer && sg == 0) scale_out[i] = mu;
     } else if (writer) {
 #pragma unroll
       for (int j = 0; j < SEG; ++j) dst[(size_t)j * LD] = (CT)(x[j] < 0.f ? 1 : 0);
+      if (sg == 0) scale_out[i] = mu;
     }
-    if (writer && sg == 0) scale_out[i] = mu;
   } else {
     const float nf = (float)((1 << (b - 1)) - 1);
     float best = __builtin_inff();
@@ -332,9 +340,6 @@ __device__ __forceinline__ void fit_rows(LoadRow load_row, const uint8_t* bits, 
     // complement, which the truncating store keeps
     constexpr float M = 12582912.0f;
     const float lo = M - nf, hi = M + nf;
-    auto code = [&](float v) {
-      return (CT)__builtin_bit_cast(uint32_t, __builtin_amdgcn_fmed3f(v * inv + M, lo, hi));
-    };
     if constexpr (QUADS) {
       if (valid) {
 #pragma unroll
@@ -343,14 +348,21 @@ __device__ __forceinline__ void fit_rows(LoadRow load_row, const uint8_t* bits, 
           const float4 v = load_quad(i, sg, c4);
           const float xv[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
-          for (int e = 0; e < 4; ++e) dst[(size_t)(4 * c4 + e) * LD] = code(xv[e]);
+          for (int e = 0; e < 4; ++e) {
+            const float c = __builtin_amdgcn_fmed3f(xv[e] * inv + M, lo, hi);
+            dst[(size_t)(4 * c4 + e) * LD] = (CT)__builtin_bit_cast(uint32_t, c);
+          }
         }
       }
+      if (writer && sg == 0) scale_out[i] = dh;
     } else if (writer) {
 #pragma unroll
-      for (int j = 0; j < SEG; ++j) dst[(size_t)j * LD] = code(x[j]);
+      for (int j = 0; j < SEG; ++j) {
+        const float c = __builtin_amdgcn_fmed3f(x[j] * inv + M, lo, hi);
+        dst[(size_t)j * LD] = (CT)__builtin_bit_cast(uint32_t, c);
+      }
+      if (sg == 0) scale_out[i] = dh;
     }
-    if (writer && sg == 0) scale_out[i] = dh;
   }
   if (diag != nullptr) {
     // all lanes have reconverged here
@@ -670,7 +682,7 @@ __device__ __forceinline__ void requant_head(const KParams& p, int bh, RequantLd
     fit_rows<DK, DV, true, PAIRS>(rebuild, sm.nb, sm.perm, sm.phi, sm.Ct, sm.sc16, p.diag_fit);
   } else {
     __syncthreads();
-    width_order<DK>(sm.nb, sm.perm, sm.os, r0, r0 + ROWS, p.bmax);
+    width_order<DK, (PAIRS > 1)>(sm.nb, sm.perm, sm.os, r0, r0 + ROWS, p.bmax);
     const float* S = p.ws_s32 + (size_t)bh * DK * DV;
     auto staged = [&](int i, int sg, float (&x)[SEG]) {
       load_staged<DV>(sx, min(max(i - r0, 0), ROWS - 1), sg, x);

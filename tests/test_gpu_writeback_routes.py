@@ -31,7 +31,7 @@ def _cfg(B, H, d, **kw):
 @pytest.mark.parametrize("B,H,d,kw", [
     (1, 1, 64, {}), (1, 3, 64, dict(b_min=1, mean_bits=1.75)), (8, 32, 64, {}), (8, 33, 64, dict(mean_bits=3.0)),
     (32, 32, 64, {}), (33, 32, 64, dict(b_min=1, mean_bits=2.5)), (33, 32, 64, dict(b_max=12, mean_bits=7.0)), (1, 1, 128, dict(b_min=1, mean_bits=2.5)), (2, 32, 128, dict(group_rows=64)), (5, 13, 128, {}),
-    (8, 32, 128, dict(mean_bits=3.0)), (2, 2, 128, dict(b_max=16, mean_bits=9.0)), (2, 2, 64, dict(b_max=16, mean_bits=8.5)),
+    (8, 32, 128, dict(mean_bits=3.0)), (9, 29, 128, {}), (2, 2, 128, dict(b_max=16, mean_bits=9.0)), (2, 2, 64, dict(b_max=16, mean_bits=8.5)),
     (2, 6, 128, dict(group_rows=3 * 128, b_min=1)), (3, 5, 128, dict(scope=1, b_min=1, mean_bits=2.0)),
 ])
 def test_routes_write_the_same_records(B, H, d, kw):
