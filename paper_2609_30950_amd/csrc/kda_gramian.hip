@@ -26,16 +26,20 @@ namespace kda {
 // 311 us (5.2 TB/s) at B = 32, H = 32, d_k = 128, W = 1024.
 constexpr int WG_NW = 4;   // waves per block
 constexpr int WG_U = 4;    // tokens per wave and tile
+// Blocks per launch: a grid holds fewer than 2^32 threads, and four threads per
+// row reach that at 2^30 rows (B H d_k), so larger calls take several launches.
+constexpr long long WG_GRID = 1ll << 22;
 
 template <bool PER_HEAD, bool ERASE>
-__global__ void __launch_bounds__(WG_NW* WAVE) k_window_gamma(int W, int H, int DKr, int C, const float* q,
+__global__ void __launch_bounds__(WG_NW* WAVE) k_window_gamma(long long first, int W, int H, int DKr, int C, const float* q,
                                                               const float* s, const float* beta,
                                                               const float* k, double* gamma) {
   constexpr int TILE = WG_NW * WG_U;
   __shared__ double lam[2][TILE][WAVE], q2[2][TILE][WAVE];
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE), lane = lane_id();
   const int nrb = DKr / WAVE;
-  const int bh = blockIdx.x / nrb, i = (blockIdx.x % nrb) * WAVE + lane;
+  const long long blk = first + blockIdx.x;
+  const int bh = (int)(blk / nrb), i = (int)(blk % nrb) * WAVE + lane;
   const int b = bh / H, h = bh % H;
   float qv[WG_U], kv[WG_U], sv[WG_U], bv[WG_U];
   auto issue = [&](int t0) {   // inputs of this wave's tokens of the tile at t0 (clamped to the window)
@@ -257,9 +261,14 @@ hipError_t launch_exact_gamma(const KParams& p, int W, int C, const float* q, co
 
 hipError_t launch_window_gamma(const KParams& p, int W, int C, const float* q, const float* s,
                                const float* beta, const float* k, double* gamma, hipStream_t st) {
-  const unsigned nblk = (unsigned)(p.B * p.H * (p.dk / WAVE));
+  const long long nblk = (long long)p.B * p.H * (p.dk / WAVE);
   const auto go = [&](auto kernel) {
-    return launch("weights", kernel, nblk, WG_NW * WAVE, 0, st, W, p.H, p.dk, C, q, s, beta, k, gamma);
+    hipError_t e = hipSuccess;
+    for (long long first = 0; first < nblk && e == hipSuccess; first += WG_GRID) {
+      const unsigned n = (unsigned)(nblk - first < WG_GRID ? nblk - first : WG_GRID);
+      e = launch("weights", kernel, n, WG_NW * WAVE, 0, st, first, W, p.H, p.dk, C, q, s, beta, k, gamma);
+    }
+    return e;
   };
   if (p.per_head) return p.no_erase ? go(k_window_gamma<true, false>) : go(k_window_gamma<true, true>);
   return p.no_erase ? go(k_window_gamma<false, false>) : go(k_window_gamma<false, true>);

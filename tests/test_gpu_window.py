@@ -28,3 +28,23 @@ def test_window_weights_at_tile_edges(Wn, C, d, per_head, erase):
     # sums of non-negative terms in the same order; exp arguments of magnitude
     # below 10, so each factor agrees within some 20 ulp and 50 of them within 2e-13
     np.testing.assert_allclose(host(g).reshape(B, H, d), want, rtol=1e-12)
+
+
+def test_window_weights_of_more_rows_than_one_grid():
+    """2^30 + 4096 rows (four threads each: more than a grid's 2^32 - 1 threads, so several
+    launches): all rows of a two-token window, in closed form."""
+    B, H, d = 2**18 + 1, 64, 64
+    n = B * H
+    cfg = K.Config(B=B, H=H, d_k=d, d_v=d, group_rows=d, decay_per_head=1, no_erase=0)
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    q, k = (torch.rand(B, 2, H, d, generator=gen, device="cuda") for _ in range(2))
+    s, beta = (torch.rand(B, 2, H, generator=gen, device="cuda") for _ in range(2))
+    g = torch.full((B, H, d), -1.0, dtype=torch.float64, device="cuda")
+    assert n * d == 2**30 + 4096
+    K.kda_weights(cfg, 2, 1, q, s, beta, k, g)
+    for b0 in range(0, B, 2**14):
+        sl = slice(b0, b0 + 2**14)
+        q1, k1, s1, b1 = (x[sl, 1].double() for x in (q, k, s, beta))
+        lam = torch.exp(-2 * s1[..., None] - (b1 * (2 - b1))[..., None] * k1 * k1)
+        # one product of three float64 factors: a few ulp, as above
+        torch.testing.assert_close(g[sl], q1 * q1 * lam / 2, rtol=1e-12, atol=0.0)
