@@ -150,6 +150,30 @@ __device__ __forceinline__ float ternary_code(float x, float K, float nKth) {
   return __builtin_amdgcn_fmed3f(__builtin_fmaf(fabsf(x), K, nKth), 0.f, 1.f);
 }
 
+// Squared error of a segment coded with scale d and levels -nf .. nf, summed in
+// column order.  ternary: the form for nf = 1 (the same float32 value).
+__device__ __forceinline__ float segment_error(const float (&x)[SEG], float d, float nf, bool ternary) {
+  const float inv = recip_f16_value(d);
+  float err = 0.f;
+  if (ternary) {
+    float K, nKth;
+    ternary_threshold(d, inv, K, nKth);
+#pragma unroll
+    for (int j = 0; j < SEG; ++j) {
+      const float e = __builtin_fmaf(-ternary_code(x[j], K, nKth), d, fabsf(x[j]));
+      err = __builtin_fmaf(e, e, err);
+    }
+  } else {
+#pragma unroll
+    for (int j = 0; j < SEG; ++j) {
+      const float c = __builtin_amdgcn_fmed3f(__builtin_rintf(x[j] * inv), -nf, nf);
+      const float e = __builtin_fmaf(-c, d, x[j]);
+      err = __builtin_fmaf(e, e, err);
+    }
+  }
+  return err;
+}
+
 // Quantise the rows of a row-major float32 state S[DK][DV] (device memory)
 // with widths bits[] (method: see the top of this file and include/kda.h).
 // Thread t handles the 64-column segment t % (DV/64) of row
@@ -244,10 +268,10 @@ __device__ __forceinline__ void fit_rows(LoadRow load_row, const uint8_t* bits, 
     const float nf = (float)((1 << (b - 1)) - 1);
     float best = __builtin_inff();
     int mb = N_FIT - 1;
+    // waves whose rows all have width 2 take the three-operation form of the
+    // same evaluation (ternary_threshold)
+    const bool ternary = __all(b == 2);
     if constexpr (PAIRS == 1) {
-      // waves whose rows all have width 2 take the three-operation form of
-      // the same evaluation (ternary_threshold)
-      const bool ternary = __all(b == 2);
       // factors read through one running pointer: the read after the last
       // candidate (m = 0) lands on the previous width's last factor (b >= 2
       // here), in the table and unused
@@ -259,25 +283,7 @@ __device__ __forceinline__ void fit_rows(LoadRow load_row, const uint8_t* bits, 
         const float emax = __builtin_fmaf(-nf, d, mx);
         if (emax >= 0.f && emax * emax > best) break;   // row-uniform decision
         ++evals;
-        const float inv = recip_f16_value(d);
-        float err = 0.f;
-        if (ternary) {
-          float K, nKth;
-          ternary_threshold(d, inv, K, nKth);
-#pragma unroll
-          for (int j = 0; j < SEG; ++j) {
-            const float e = __builtin_fmaf(-ternary_code(x[j], K, nKth), d, fabsf(x[j]));
-            err = __builtin_fmaf(e, e, err);
-          }
-        } else {
-#pragma unroll
-          for (int j = 0; j < SEG; ++j) {
-            const float c = __builtin_amdgcn_fmed3f(__builtin_rintf(x[j] * inv), -nf, nf);
-            const float e = __builtin_fmaf(-c, d, x[j]);
-            err = __builtin_fmaf(e, e, err);
-          }
-        }
-        err = seg_combine<SEGS>(err);
+        const float err = seg_combine<SEGS>(segment_error(x, d, nf, ternary));
         if (err <= best) { best = err; mb = m; }
       }
     } else {
@@ -300,15 +306,7 @@ __device__ __forceinline__ void fit_rows(LoadRow load_row, const uint8_t* bits, 
           skip = half == q ? stop[q] : skip;
         }
         if (!skip) ++evals;
-        const float inv = recip_f16_value(d);
-        float err = 0.f;
-#pragma unroll
-        for (int j = 0; j < SEG; ++j) {
-          const float c = __builtin_amdgcn_fmed3f(__builtin_rintf(x[j] * inv), -nf, nf);
-          const float e = __builtin_fmaf(-c, d, x[j]);
-          err = __builtin_fmaf(e, e, err);
-        }
-        err = seg_combine_p<SEGS, PAIRS>(err);
+        const float err = seg_combine_p<SEGS, PAIRS>(segment_error(x, d, nf, ternary));
         // every lane of the step merges the errors in candidate order
         float eq[PAIRS];
         if constexpr (PAIRS == 2) {

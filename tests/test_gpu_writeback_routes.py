@@ -33,6 +33,8 @@ def _cfg(B, H, d, **kw):
     (32, 32, 64, {}), (33, 32, 64, dict(b_min=1, mean_bits=2.5)), (33, 32, 64, dict(b_max=12, mean_bits=7.0)), (1, 1, 128, dict(b_min=1, mean_bits=2.5)), (2, 32, 128, dict(group_rows=64)), (5, 13, 128, {}),
     (8, 32, 128, dict(mean_bits=3.0)), (9, 29, 128, {}), (2, 2, 128, dict(b_max=16, mean_bits=9.0)), (2, 2, 64, dict(b_max=16, mean_bits=8.5)),
     (2, 6, 128, dict(group_rows=3 * 128, b_min=1)), (3, 5, 128, dict(scope=1, b_min=1, mean_bits=2.0)),
+    # rows of two bits only: the fit's ternary form, with four lanes against one and two
+    (5, 13, 128, dict(mean_bits=2.0)), (8, 32, 128, dict(mean_bits=2.25)), (9, 32, 64, dict(mean_bits=2.0)),
 ])
 def test_routes_write_the_same_records(B, H, d, kw):
     cfg = _cfg(B, H, d, **kw)
@@ -64,19 +66,22 @@ def test_routes_at_256(B):
         assert torch.equal(ra.view(B, -1), rb) and torch.equal(oa, ob)
 
 
-@pytest.mark.parametrize("d,B,H,bmax", [(64, 33, 32, 8), (64, 33, 32, 16), (128, 9, 29, 8), (128, 9, 29, 16),
-                                        (128, 23, 28, 8)])
-def test_pack_routes_write_the_same_records(d, B, H, bmax):
+@pytest.mark.parametrize("d,B,H,bmin,bmax", [
+    (64, 33, 32, 1, 8), (64, 33, 32, 1, 16), (128, 9, 29, 1, 8), (128, 9, 29, 1, 16), (128, 23, 28, 1, 8),
+    # rows of two bits only: the ternary form with one, two and four lanes
+    (64, 33, 32, 2, 2), (128, 9, 29, 2, 2), (128, 23, 28, 2, 2),
+])
+def test_pack_routes_write_the_same_records(d, B, H, bmin, bmax):
     # more than 256 and 640 (d = 128) or 1024 (d = 64) heads in one call against the
     # same heads in calls of few (whose route the codec tests pin to the oracle)
     g = torch.Generator(device="cuda").manual_seed(d + B)
     S = torch.randn(B, H, d, d, generator=g, device="cuda") * torch.exp(4 * torch.randn(B, H, d, 1, generator=g, device="cuda"))
     S[0, 0, 1] = 0.0
     S[1, :, 2, ::3] = -0.0
-    bits = torch.randint(1, bmax + 1, (B, H, d), generator=g, device="cuda").to(torch.uint8)
+    bits = torch.randint(bmin, bmax + 1, (B, H, d), generator=g, device="cuda").to(torch.uint8)
     s_hat = torch.rand(B, H, d, generator=g, device="cuda").double() + 1e-4
     r = torch.rand(B, H, d, generator=g, device="cuda").double() / d
-    cfg, one = (_cfg(n, H, d, b_min=1, b_max=bmax, mean_bits=(1 + bmax) / 2) for n in (B, 1))
+    cfg, one = (_cfg(n, H, d, b_min=bmin, b_max=bmax, mean_bits=(bmin + bmax) / 2) for n in (B, 1))
     # outside a record's meaningful bytes nothing is written, inside everything:
     # start from ones
     ra = torch.full_like(K.new_records(cfg), 255)
