@@ -684,7 +684,6 @@ __device__ __forceinline__ float rowblock_max(float v) {
   return v;
 }
 
-//
 // A block is d_k / 32 waves that run the recurrence and as many that feed them:
 // these form the row scalars of the next TS tokens (with the float64
 // exponentials) and v in LDS, carry the EMA statistics (slice 0) and store the
@@ -693,10 +692,16 @@ __device__ __forceinline__ float rowblock_max(float v) {
 // issues an instruction every 4.9 cycles at best (128 per token); the staging
 // between its tokens, and the row scalars of a token read from LDS just before
 // their use, took as long again: 1550 -> 995 cycles per token, 50.8 -> 38.4 us
-// per 64 tokens at B = 4, H = 32, d_k = 128.
+// per 64 tokens at B = 4, H = 32, d_k = 128.  Large grids gain as well at 128
+// (256 tokens with four write-backs, 256 heads 400 -> 338 us, 2048 heads 2372 ->
+// 1986).  At d_k = 64 a batch of eight tokens would hold 109 registers and four
+// blocks per compute unit: large grids, bound by issue, then lost (1024 heads
+// 395 -> 399 us, 1280 heads 561 -> 586, 4096 heads 1344 -> 1364).  Four tokens
+// need 90 registers, five blocks fit: 392, 513 and 1271 us, and 32 heads 274 ->
+// 189 (eight: 207).
 template <int DK>
 struct PcSmem {
-  static constexpr int TS = 8;
+  static constexpr int TS = DK == 64 ? 4 : 8;
   static constexpr int NRB = DK / ROW_BLOCK;
   float4 rq[2][TS][DK];     // {fl32(exp(-s)), k, fl32(beta k), q} of (token, row)
   float v[2][TS][SLICE];
@@ -705,7 +710,7 @@ struct PcSmem {
 };
 
 template <int DK>   // prefill inputs are bf16
-__global__ void __launch_bounds__(4 * DK) __attribute__((amdgpu_waves_per_eu(4))) k_chunk_cols(KParams p) {
+__global__ void __launch_bounds__(4 * DK) __attribute__((amdgpu_waves_per_eu(DK == 64 ? 5 : 4))) k_chunk_cols(KParams p) {
   constexpr int NRB = DK / ROW_BLOCK;       // row blocks = recurrence waves per block
   constexpr int CPW = WAVE / NRB;           // columns per wave
   constexpr int TS = PcSmem<DK>::TS;

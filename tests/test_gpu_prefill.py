@@ -93,6 +93,20 @@ def test_prefill_outputs_match_truth_within_chunk():
     assert worst <= 1e-3
 
 
+@pytest.mark.parametrize("d,T", [(64, 1), (64, 3), (64, 4), (64, 5), (64, 8), (64, 9), (64, 13), (128, 7), (128, 8),
+                                 (128, 9), (128, 16), (128, 17), (128, 25)])
+def test_prefill_batch_edges(d, T):
+    """Intervals that end at, before and after a staged batch of tokens (4 at
+    d_k = 64, 8 at 128), on a warm record, against the oracle."""
+    w = W.sized(W.WORKLOADS["prefill"], B=1, H=2, dk=d, dv=d, G=d)
+    kc, oc = _cfgs(w)
+    warm = W.tokens(w, 0, 8)
+    st0, _ = step.warm_state(warm["q"], warm["k"], warm["v"], warm["s"], warm["beta"], oc)
+    stg, st, og, o_or = _run(w, st0, W.tokens(w, 8, 8 + T), 64)
+    _check_state(stg, st, f"prefill edges d={d} T={T}")
+    assert np.max(np.abs(og - o_or)) <= 1e-6 * np.max(np.abs(o_or))
+
+
 def test_prefill_decode_shape_layer_budget():
     w = W.sized(W.WORKLOADS["prefill"], B=1, T=80)
     kc, oc = _cfgs(w)
