@@ -1187,12 +1187,12 @@ hipError_t launch_prefill(KParams p, int C, hipStream_t st) {
 
 template <int DK, int PAIRS, int PARTS, bool STAGE>
 static hipError_t launch_pack_t(const KParams& p, const float* S, const uint8_t* bits, const double* s_hat,
-                                const double* r, unsigned ntok, hipStream_t st) {
+                                const double* r, unsigned ntok, hipStream_t st,
+                                int nth = requant_threads(DK, DK, PAIRS, PARTS)) {
   const int nblk = p.B * p.H * PARTS;
-  constexpr int NTH = requant_threads(DK, DK, PAIRS, PARTS);
   return DK > 128 || p.bmax <= 8
-             ? launch("pack", k_pack<DK, true, PAIRS, PARTS, STAGE>, nblk, NTH, 0, st, p, S, bits, s_hat, r, ntok)
-             : launch("pack", k_pack<DK, (DK > 128), PAIRS, PARTS, STAGE>, nblk, NTH, 0, st, p, S, bits, s_hat, r, ntok);
+             ? launch("pack", k_pack<DK, true, PAIRS, PARTS, STAGE>, nblk, nth, 0, st, p, S, bits, s_hat, r, ntok)
+             : launch("pack", k_pack<DK, (DK > 128), PAIRS, PARTS, STAGE>, nblk, nth, 0, st, p, S, bits, s_hat, r, ntok);
 }
 
 // Lanes per row segment, blocks per head and staging by the number of heads
@@ -1205,14 +1205,16 @@ static hipError_t launch_pack_t(const KParams& p, const float* S, const uint8_t*
 // d_k = 64 (a wave of single lanes holds all 64 rows, and pays the longest scan
 // of any; one lane / two / four, staged): 256 heads: 18.9 13.2 10.8, 1024: 24.6
 // 18.0 16.5, 2048: 36.9 26.1 29.1.  d_k = 256: a thread per row segment (1024)
-// instead of two segments in turn: 41.8 -> 36.7 at 256 heads.
+// instead of two segments in turn (512) while a compute unit holds one block:
+// 41.3 -> 35.2 at 256 heads; 272: 58.3 against 65.0, 512: 59.9 against 68.0.
 hipError_t launch_pack(const KParams& p, const float* S, const uint8_t* bits, const double* s_hat,
                        const double* r, unsigned ntok, hipStream_t st) {
   const int nbh = p.B * p.H;
   if (p.dk == 64)
     return nbh <= 1024 ? launch_pack_t<64, 4, 1, true>(p, S, bits, s_hat, r, ntok, st)
                        : launch_pack_t<64, 2, 1, false>(p, S, bits, s_hat, r, ntok, st);
-  if (p.dk == 256) return launch_pack_t<256, 1, 1, false>(p, S, bits, s_hat, r, ntok, st);
+  if (p.dk == 256)
+    return launch_pack_t<256, 1, 1, false>(p, S, bits, s_hat, r, ntok, st, nbh <= 256 ? requant_threads(256, 256, 1) : 512);
   if (nbh <= 256) return launch_pack_t<128, 4, 2, true>(p, S, bits, s_hat, r, ntok, st);
   return nbh <= 640 ? launch_pack_t<128, 2, 2, false>(p, S, bits, s_hat, r, ntok, st)
                     : launch_pack_t<128, 1, 1, false>(p, S, bits, s_hat, r, ntok, st);

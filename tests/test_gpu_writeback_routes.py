@@ -68,11 +68,12 @@ def test_routes_at_256(B):
 
 @pytest.mark.parametrize("d,B,H,bmin,bmax", [
     (64, 33, 32, 1, 8), (64, 33, 32, 1, 16), (128, 9, 29, 1, 8), (128, 9, 29, 1, 16), (128, 23, 28, 1, 8),
+    (256, 17, 16, 1, 8),   # 272 heads: two segments per thread instead of one
     # rows of two bits only: the ternary form with one, two and four lanes
     (64, 33, 32, 2, 2), (128, 9, 29, 2, 2), (128, 23, 28, 2, 2),
 ])
 def test_pack_routes_write_the_same_records(d, B, H, bmin, bmax):
-    # more than 256 and 640 (d = 128) or 1024 (d = 64) heads in one call against the
+    # more than 256 and 640 (d = 128), 1024 (d = 64) or 256 (d = 256) heads in one call against the
     # same heads in calls of few (whose route the codec tests pin to the oracle)
     g = torch.Generator(device="cuda").manual_seed(d + B)
     S = torch.randn(B, H, d, d, generator=g, device="cuda") * torch.exp(4 * torch.randn(B, H, d, 1, generator=g, device="cuda"))
