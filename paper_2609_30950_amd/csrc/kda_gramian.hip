@@ -26,8 +26,8 @@ namespace kda {
 // 311 us (5.2 TB/s) at B = 32, H = 32, d_k = 128, W = 1024.
 constexpr int WG_NW = 4;   // waves per block
 constexpr int WG_U = 4;    // tokens per wave and tile
-// Blocks per launch: a grid holds fewer than 2^32 threads, and four threads per
-// row reach that at 2^30 rows (B H d_k), so larger calls take several launches.
+// Blocks per launch: a grid holds fewer than 2^32 threads, so calls of more than
+// 2^30 rows (B H d_k; 2^28 in tiles) take several launches.
 constexpr long long WG_GRID = 1ll << 22;
 
 template <bool PER_HEAD, bool ERASE>
@@ -80,6 +80,31 @@ __global__ void __launch_bounds__(WG_NW* WAVE) k_window_gamma(long long first, i
     }
   }
   if (w == 0) gamma[(size_t)bh * DKr + i] = acc / (double)W;
+}
+
+// The same with one thread per row and the tokens in turn, for windows too short
+// to fill tiles and grids large enough to hide a token's chain (launch_window_gamma).
+template <bool PER_HEAD, bool ERASE>
+__global__ void __launch_bounds__(WG_NW* WAVE) k_window_gamma_rows(long long first, long long rows, int W, int H, int DKr, int C,
+                                                                    const float* q, const float* s, const float* beta,
+                                                                    const float* k, double* gamma) {
+  const long long id = (first + blockIdx.x) * (WG_NW * WAVE) + threadIdx.x;
+  if (id >= rows) return;
+  const int bh = (int)(id / DKr), i = (int)(id % DKr);
+  const int b = bh / H, h = bh % H;
+  double A = 0.0, acc = 0.0;
+  int ph = 1 % C;   // t % C
+  for (int t = 1; t < W; ++t) {
+    const size_t tok = ((size_t)b * W + t) * H + h;
+    const float sv = PER_HEAD ? s[tok] : s[tok * DKr + i];
+    const double y = ERASE ? erase_sample(k[tok * DKr + i], beta[tok]) : 0.0;
+    const double qq = (double)q[tok * DKr + i];
+    const double chi = ph == 0 ? 1.0 : 0.0;   // write-back after token t - 1
+    ph = ph + 1 == C ? 0 : ph + 1;
+    A = exp(-2.0 * (double)sv - y) * (chi + A);
+    acc = acc + (qq * qq) * A;
+  }
+  gamma[id] = acc / (double)W;
 }
 
 // Exact Gramian weights (eq. gram with the full transition
@@ -261,17 +286,45 @@ hipError_t launch_exact_gamma(const KParams& p, int W, int C, const float* q, co
 
 hipError_t launch_window_gamma(const KParams& p, int W, int C, const float* q, const float* s,
                                const float* beta, const float* k, double* gamma, hipStream_t st) {
-  const long long nblk = (long long)p.B * p.H * (p.dk / WAVE);
-  const auto go = [&](auto kernel) {
+  // Rows in turn up to a token per 8192 rows of the call, at least four: a tile
+  // is 16 tokens' exponentials and one trip to memory however few are left of
+  // it, while with that many rows the threads' own chains overlap.  us, tiles
+  // against rows in turn (rate per channel, with erasure), d = 128:
+  //   2 tokens, heads 32: 3.4 3.2   1024: 7.0 3.3   8192: 38.8 7.3
+  //   16 tokens,   256: 4.4 5.8     1024: 7.7 6.4   8192: 43.9 31.3
+  //   32 tokens,  1024: 13.2 16.1   2048: 22.0 20.0   64 tokens, 4096: 84.3 78.4
+  // With three arrays to read (q, k and s per channel) the turn comes at about 100
+  // tokens however many the rows (16384 heads: 96 tokens 453 443, 128 tokens 588
+  // 642); with one (rate per head, no erasure) at twice the length beyond 2^16
+  // rows (4096 heads: 96 tokens 84 69; 512 heads: 16 tokens 4.9 5.4).
+  const long long rows = (long long)p.B * p.H * p.dk;
+  long long in_turn_max = rows >> 13 > 4 ? rows >> 13 : 4;
+  if (!p.per_head && !p.no_erase && in_turn_max > 96) in_turn_max = 96;
+  if (p.per_head && p.no_erase && rows > 1 << 16) in_turn_max *= 2;
+  // launches of up to WG_GRID blocks of WG_NW waves
+  const auto blocks = [](long long nblk, auto go) {
     hipError_t e = hipSuccess;
-    for (long long first = 0; first < nblk && e == hipSuccess; first += WG_GRID) {
-      const unsigned n = (unsigned)(nblk - first < WG_GRID ? nblk - first : WG_GRID);
-      e = launch("weights", kernel, n, WG_NW * WAVE, 0, st, first, W, p.H, p.dk, C, q, s, beta, k, gamma);
-    }
+    for (long long first = 0; first < nblk && e == hipSuccess; first += WG_GRID)
+      e = go(first, (unsigned)(nblk - first < WG_GRID ? nblk - first : WG_GRID));
     return e;
   };
-  if (p.per_head) return p.no_erase ? go(k_window_gamma<true, false>) : go(k_window_gamma<true, true>);
-  return p.no_erase ? go(k_window_gamma<false, false>) : go(k_window_gamma<false, true>);
+  const auto tiled = [&](auto kernel) {
+    return blocks(rows / WAVE, [&](long long first, unsigned n) {
+      return launch("weights", kernel, n, WG_NW * WAVE, 0, st, first, W, p.H, p.dk, C, q, s, beta, k, gamma);
+    });
+  };
+  const auto in_turn = [&](auto kernel) {
+    return blocks((rows + WG_NW * WAVE - 1) / (WG_NW * WAVE), [&](long long first, unsigned n) {
+      return launch("weights", kernel, n, WG_NW * WAVE, 0, st, first, rows, W, p.H, p.dk, C, q, s, beta, k, gamma);
+    });
+  };
+  if (W <= in_turn_max) {
+    if (p.per_head)
+      return p.no_erase ? in_turn(k_window_gamma_rows<true, false>) : in_turn(k_window_gamma_rows<true, true>);
+    return p.no_erase ? in_turn(k_window_gamma_rows<false, false>) : in_turn(k_window_gamma_rows<false, true>);
+  }
+  if (p.per_head) return p.no_erase ? tiled(k_window_gamma<true, false>) : tiled(k_window_gamma<true, true>);
+  return p.no_erase ? tiled(k_window_gamma<false, false>) : tiled(k_window_gamma<false, true>);
 }
 
 }  // namespace kda

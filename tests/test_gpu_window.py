@@ -1,5 +1,6 @@
 """kda_weights at the edges of its token tiles (16 tokens: one, a remainder,
-a whole tile, several) against the oracle's float64 recursion."""
+a whole tile, several) and of the windows that its rows take in turn, against
+the oracle's float64 recursion and of one form against the other."""
 import numpy as np
 import pytest
 import torch
@@ -12,7 +13,7 @@ from tests._gpu import dev, host
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("Wn,C", [(1, 1), (2, 1), (16, 3), (17, 1), (18, 64), (33, 16), (50, 7)])
+@pytest.mark.parametrize("Wn,C", [(1, 1), (2, 1), (4, 1), (5, 2), (16, 3), (17, 1), (18, 64), (33, 16), (50, 7)])
 @pytest.mark.parametrize("d,per_head,erase", [(64, False, True), (128, True, False), (256, True, True),
                                               (128, False, False)])
 def test_window_weights_at_tile_edges(Wn, C, d, per_head, erase):
@@ -30,9 +31,28 @@ def test_window_weights_at_tile_edges(Wn, C, d, per_head, erase):
     np.testing.assert_allclose(host(g).reshape(B, H, d), want, rtol=1e-12)
 
 
+@pytest.mark.parametrize("Wn,C", [(7, 3), (16, 1), (17, 5), (32, 7)])
+@pytest.mark.parametrize("per_head,erase", [(False, True), (True, True), (False, False), (True, False)])
+def test_windows_of_many_rows_equal_those_of_few(Wn, C, per_head, erase):
+    """131072 rows take windows of up to 16 or 32 tokens in turn, 4096 rows only up to four:
+    the same operations per row in the same order, so the same bits."""
+    B, H, d = 32, 32, 128
+    gen = torch.Generator(device="cuda").manual_seed(Wn)
+    q, k = (torch.randn(B, Wn, H, d, generator=gen, device="cuda") for _ in range(2))
+    s = torch.rand(*((B, Wn, H) if per_head else (B, Wn, H, d)), generator=gen, device="cuda")
+    beta = torch.rand(B, Wn, H, generator=gen, device="cuda")
+    many, few = (torch.full((B, H, d), -1.0, dtype=torch.float64, device="cuda") for _ in range(2))
+    cfg, one = (K.Config(B=n, H=H, d_k=d, d_v=d, group_rows=d, decay_per_head=int(per_head), no_erase=int(not erase))
+                for n in (B, 1))
+    K.kda_weights(cfg, Wn, C, q, s, beta, k, many)
+    for b in range(B):
+        K.kda_weights(one, Wn, C, q[b], s[b], beta[b], k[b], few[b])
+    assert torch.equal(many, few)
+
+
 def test_window_weights_of_more_rows_than_one_grid():
-    """2^30 + 4096 rows (four threads each: more than a grid's 2^32 - 1 threads, so several
-    launches): all rows of a two-token window, in closed form."""
+    """2^30 + 4096 rows (more blocks than a launch takes, so two launches): all
+    rows of a two-token window, in closed form."""
     B, H, d = 2**18 + 1, 64, 64
     n = B * H
     cfg = K.Config(B=B, H=H, d_k=d, d_v=d, group_rows=d, decay_per_head=1, no_erase=0)
