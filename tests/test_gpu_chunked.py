@@ -151,8 +151,9 @@ def test_chunk_per_head_decay_head_scope():
 
 def test_chunk_d128_head_scope_two_groups_per_head():
     """d = 128 with groups of 64 rows (two per head) and the per-head budget:
-    the apply blocks form both groups' weights and each requantisation block
-    selects its own head's widths."""
+    the apply blocks form both groups' weights, and a selection per head precedes
+    the write-back (of more than 64 heads the write-back's blocks select their
+    head's widths themselves: test_gpu_writeback_routes)."""
     w = W.sized(W.WORKLOADS["prefill"], B=2, H=3, G=64)
     kc, oc = _cfgs(w, scope=1)
     warm = W.tokens(w, 0, 16)

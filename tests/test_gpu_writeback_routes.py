@@ -2,8 +2,9 @@
 lanes per group of factors, a block per head) are one function: the step on the
 workspace, whose route depends on B H, against kda_step_noalloc, which always
 rebuilds the state from the record in a block per head (d_k <= 128), and one
-launch of many heads against the same heads in launches of few (d_k = 256).
-Head counts lie at the edges of the routes' ranges."""
+launch of many heads against the same heads in launches of few (d_k = 256, the
+prefill's intervals, the codec).  Head counts lie at the edges of the routes'
+ranges."""
 import pytest
 import torch
 
@@ -33,6 +34,8 @@ def _cfg(B, H, d, **kw):
     (32, 32, 64, {}), (33, 32, 64, dict(b_min=1, mean_bits=2.5)), (33, 32, 64, dict(b_max=12, mean_bits=7.0)), (1, 1, 128, dict(b_min=1, mean_bits=2.5)), (2, 32, 128, dict(group_rows=64)), (5, 13, 128, {}),
     (8, 32, 128, dict(mean_bits=3.0)), (9, 29, 128, {}), (2, 2, 128, dict(b_max=16, mean_bits=9.0)), (2, 2, 64, dict(b_max=16, mean_bits=8.5)),
     (2, 6, 128, dict(group_rows=3 * 128, b_min=1)), (3, 5, 128, dict(scope=1, b_min=1, mean_bits=2.0)),
+    # four lanes with int16 codes
+    (5, 13, 128, dict(b_max=12, mean_bits=7.0)), (9, 32, 64, dict(b_max=16, mean_bits=8.5)),
     # rows of two bits only: the fit's ternary form, with four lanes against one and two
     (5, 13, 128, dict(mean_bits=2.0)), (8, 32, 128, dict(mean_bits=2.25)), (9, 32, 64, dict(mean_bits=2.0)),
 ])
@@ -49,9 +52,10 @@ def test_routes_write_the_same_records(B, H, d, kw):
         assert torch.equal(ra, rb) and torch.equal(oa, ob)
 
 
-@pytest.mark.parametrize("B", [2, 3, 6, 7])
+@pytest.mark.parametrize("B", [2, 3, 6, 7, 17])
 def test_routes_at_256(B):
-    # heads per launch: 32 (one round, widths selected inside), 48 and 96, 112 (a block per head)
+    # heads per launch: 32 (one round, widths selected inside), 48 and 96, 112 (a block per head),
+    # 272 (the same with two segments per thread)
     H, d = 16, 256
     cfg, one = _cfg(B, H, d, b_min=1, mean_bits=2.5), _cfg(1, H, d, b_min=1, mean_bits=2.5)
     ws, ws1 = K.new_workspace(cfg), K.new_workspace(one)
@@ -64,6 +68,39 @@ def test_routes_at_256(B):
             K.kda_step(one, rb[b], *(a[b].contiguous() for a in x), ob[b], ws1)
         say(f"routes d=256 B={B} t={t}")
         assert torch.equal(ra.view(B, -1), rb) and torch.equal(oa, ob)
+
+
+PREFILLS = [
+    # 128: more than 64 heads (four lanes, two blocks per head; chunked: each selects its widths)
+    (5, 13, 128, {}), (5, 13, 128, dict(b_max=12, mean_bits=7.0, group_rows=64)),
+    (5, 13, 128, dict(scope=1, b_min=1, mean_bits=2.5, group_rows=64)), (5, 13, 128, dict(scope=1, b_max=16, mean_bits=9.0)),
+    (3, 24, 128, dict(group_rows=12 * 128, b_min=1)),
+    # 64: more than 256 heads; 256: more than 32 (a block per head)
+    (9, 29, 64, {}), (9, 29, 64, dict(b_max=16, mean_bits=8.5)), (3, 11, 256, dict(b_min=1, mean_bits=2.5)),
+]
+
+
+@pytest.mark.parametrize("B,H,d,kw,chunked",
+                         [(*p, c) for p in PREFILLS for c in ((0, 1) if p[2] <= 128 else (0,))])
+def test_prefill_routes_write_the_same_records(B, H, d, kw, chunked):
+    # all sequences in one call against calls of one sequence (one lane per clip factor)
+    C, T = 16, 40
+    cfg, one = (_cfg(n, H, d, chunked=chunked, **kw) for n in (B, 1))
+    g = torch.Generator(device="cuda").manual_seed(d + H)
+    unit = lambda: torch.nn.functional.normalize(torch.randn(B, T, H, d, generator=g, device="cuda"), dim=-1).bfloat16()  # noqa: E731
+    q, k = unit(), unit()
+    v = torch.randn(B, T, H, d, generator=g, device="cuda")
+    v[-1] *= torch.exp(3 * torch.randn(T, H, d, generator=g, device="cuda"))   # heavy tails in the last sequence
+    v[0, :, 0] = 0.0                                                           # a head whose state stays zero
+    x = (q, k, v.bfloat16(), torch.exp(-7 * torch.rand(B, T, H, d, generator=g, device="cuda")),
+         torch.sigmoid(torch.randn(B, T, H, generator=g, device="cuda")))
+    ra, rb = K.new_records(cfg), K.new_records(cfg).view(B, -1)
+    oa, ob = (torch.empty(B, T, H, d, device="cuda") for _ in range(2))
+    K.kda_prefill(cfg, T, C, ra, *x, oa, K.new_workspace(cfg))
+    ws = K.new_workspace(one)
+    for b in range(B):
+        K.kda_prefill(one, T, C, rb[b], *(a[b] for a in x), ob[b], ws)
+    assert torch.equal(ra.view(B, -1), rb) and torch.equal(oa, ob)
 
 
 @pytest.mark.parametrize("d,B,H,bmin,bmax", [
