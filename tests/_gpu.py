@@ -97,19 +97,25 @@ def ws_offsets(B, H, dk, dv):
 
 def decode_state_gpu(kc, recs_before, ws, sel=None):
     """float32 state a decode step's write-back quantised, from the GPU's
-    own values: d_k <= 128 hands the token's vectors a, g, w to the
-    write-back, which forms S = fma(g_i, w_j, fl32(a_i x^_ij)) from the
-    record's dequantised state x^ (decoded here by kda_unpack_state on a copy
-    of the records taken before the step); d_k = 256 leaves S itself.
+    own values.  d_k = 256 leaves S itself.  d_k <= 128 hands the token's
+    vectors a, g, w to the write-back of many heads, which forms
+    S = fma(g_i, w_j, fl32(a_i x^_ij)) from the record's dequantised state x^
+    (decoded here by kda_unpack_state on a copy of the records taken before
+    the step); the write-back of few heads (up to 256 of 128, 1024 of 64)
+    quantises a state that the statistics pass left: that one is returned
+    then, and has to be the same.
     sel: the sequences to return (all if None)."""
     import paper_2609_30950_amd as K
     from oracle.fp import fma32
     B, H, dk, dv = kc.B, kc.H, kc.d_k, kc.d_v
     off = ws_offsets(B, H, dk, dv)
     sel = list(range(B)) if sel is None else list(sel)
-    if dk > 128:
-        a = ws[off["s32"]:off["s32"] + B * H * dk * dv * 4].view(torch.float32)
-        return host(a.view(B, H, dk, dv)[sel]).copy()
+    left = None
+    if B * H <= {64: 1024, 128: 256}.get(dk, B * H):
+        left = ws[off["s32"]:off["s32"] + B * H * dk * dv * 4].view(torch.float32)
+        left = host(left.view(B, H, dk, dv)[sel]).copy()
+        if dk > 128:
+            return left
     X = torch.empty(B * H * dk * dv, dtype=torch.float32, device="cuda")
     K.kda_unpack_state(kc, recs_before, X)
     X = host(X.view(B, H * dk * dv)[sel]).reshape(-1, dk, dv)
@@ -117,7 +123,9 @@ def decode_state_gpu(kc, recs_before, ws, sel=None):
     hv = host(hv.view(B, H * (dv + 2 * dk))[sel]).reshape(-1, dv + 2 * dk)
     wv, a, g = hv[:, :dv], hv[:, dv:dv + dk], hv[:, dv + dk:]
     S = fma32(g[:, :, None], wv[:, None, :], (a[:, :, None] * X).astype(np.float32))
-    return S.reshape(len(sel), H, dk, dv)
+    S = S.reshape(len(sel), H, dk, dv)
+    assert left is None or np.array_equal(left, S), "the state left for the write-back is not the token's update"
+    return S if left is None else left
 
 
 def decode_gamma(st_old, x, span, erase=True, mode="ema", C=1):
