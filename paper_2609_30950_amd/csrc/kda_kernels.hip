@@ -190,13 +190,14 @@ inline size_t stats_dyn_bytes(int wc) {
 
 // What the statistics pass of a decode step leaves for the requantisation: the
 // token's vectors (a, g, w; d_k <= 128), from which it can rebuild the state
-// with the record, the float32 state, or both.
+// with the record, the float32 state, or both: the write-backs of few heads read
+// the state alone, but the vectors are part of what kda.h says the workspace
+// holds between the two halves of a step with d_k <= 128 (0.1 to 0.3 us a step).
 enum Handover { HAND_VECTORS = 1, HAND_STATE = 2 };
 
 // Decode token tok0 of one head with the state resident in registers,
-// starting from the record: the output o, the token's vectors (d_k <= 128) or
-// the float32 state after it (d_k = 256) for the requantisation, row ranges
-// and EMA rates, weights c and, for the per-head scope, the widths (with
+// starting from the record: the output o, the token's vectors or the float32
+// state after it or both (HAND) for the requantisation, row ranges and EMA rates, weights c and, for the per-head scope, the widths (with
 // alloc_sm as the allocator's LDS).  All threads of the block (2 d_k) call it.
 template <int DK, int DV, bool HEAD, int HAND>
 __device__ __forceinline__ void stats_head(const KParams& p, int bh, StatsLds<DK, DV>& sm,
@@ -1012,24 +1013,28 @@ static hipError_t launch_requant_par(const KParams& p, hipStream_t st) {
 //    further round costs as much again.  d_k = 256: up to three rounds, with a
 //    separate allocation from the second on, since there a head takes 46 us.
 //  * WB_QUAD (d_k <= 128): four lanes per factor group and two blocks per head
-//    (as the prefill) up to 256 heads of 128 (12 us at 64 to 256) and 1024 of
-//    64; from there on the compact form is the faster one (384 heads: by the
-//    mix of widths; with none of two bits and no erasure 46.5 against 48.3).
+//    (as the prefill) up to 256 heads of 128 (12 us at 64 to 256) and 1024 of 64.
 //  * WB_COMPACT / WB_HEAD: a block per head, the state rebuilt from the record
 //    (d_k <= 128) or read (256).
-// Whole steps, us, at a four-bit mean, COMPACT/HEAD, QUAD, PAR:
-//   d 128, heads 32: 36.6 28.4 22.3   64: 36.6 28.6 22.7   96: 36.7 29.1 32.8
-//          128: 36.9 29.4 33.2   256: 37.0 35.5 54.8   288: 43.6 42.2 66.3
-//          384: 44.1 43.5 77.3   512: 44.7 49.9 98.3
-//   d  64, heads 32: 35.2 23.4 19.2   256: 34.0 27.2 21.6   384: 38.5 28.0 30.8
-//          1024: 33.9 33.4 51.7   1280: 38.9 39.8   2048: 43.8 51.0 93.1
-//          (COMPACT with two lanes per row from 1024 on)
-//   d 256, heads 32: 58.5 - 31.7   64: 60.6 - 43.8   96: 62.6 - 53.8   128: 59.1 - 65.1
+// Whole steps, us, at a four-bit mean of [1, 8], COMPACT/HEAD, QUAD, PAR:
+//   d 128, heads 32: 39.8 27.1 22.3   64: 38.2 27.6 22.6   96: 38.2 28.0 29.2
+//          128: 37.9 28.4 29.7   256: 37.9 33.0 42.4   288: 43.7 41.4 49.1
+//          320: 43.7 41.9 49.9   384: 44.4 43.3 55.5   512: 44.7 48.7 67.7
+//   d  64, heads 32: 30.9 23.4 19.6   256: 29.8 24.6 20.3   320: 31.1 25.7 28.2
+//          512: 31.3 26.8 28.7   1024: 33.1 32.6 43.1   1280: 38.5 40.7 49.7
+//          2048: 43.4 51.2 70.2   (COMPACT with two lanes per row)
+//   d 256, heads 32: 51.9 - 31.0   64: 53.4 - 42.3   96: 56.2 - 52.6
+//          112: 55.3 - 60.8   256: 62.0 - 102
+// 128: the line is at 256 heads because there every mix of widths gains.  From
+// 257 to 384 it depends: with erasure QUAD is ahead by 7% (two bits) to 5% at 288
+// heads and by 1 to 3% at 384; without erasure (rate per head) by 1 to 4% at
+// 288, level at 320 and behind by 1 to 5% at 384.
 enum WriteBack { WB_COMPACT, WB_HEAD, WB_QUAD, WB_PAR };
 template <int DK>
 static WriteBack step_writeback(const KParams& p) {
   const int nbh = p.B * p.H;
-  if (p.ws_s32 == nullptr) return WB_COMPACT;   // scratch without room for a float32 state
+  // scratch without room for a float32 state (kda_step_noalloc: d_k <= 128)
+  if (DK <= 128 && p.ws_s32 == nullptr) return WB_COMPACT;
   const int par_blocks = nbh * (DK / par_rows<DK>());
   if (par_blocks <= 256 * (DK == 256 ? 3 : 1)) return WB_PAR;
   if (DK == 256) return WB_HEAD;
@@ -1067,8 +1072,11 @@ static hipError_t launch_interval_t(const KParams& p, hipStream_t st, int phases
   const bool alloc_in = wb == WB_PAR && par_blocks <= 256 && p.scope == 0 && p.G <= DK;
   hipError_t e = hipSuccess;
   if (phases & 1) {
-    e = wb == WB_COMPACT ? launch_stats<DK, DV, HAND_VECTORS>(p, st)
-                         : launch_stats<DK, DV, DK <= 128 ? HAND_VECTORS | HAND_STATE : HAND_STATE>(p, st);
+    if constexpr (DK > 128)
+      e = launch_stats<DK, DV, HAND_STATE>(p, st);
+    else
+      e = wb == WB_COMPACT ? launch_stats<DK, DV, HAND_VECTORS>(p, st)
+                           : launch_stats<DK, DV, HAND_VECTORS | HAND_STATE>(p, st);
     if (e != hipSuccess) return e;
     if (p.scope == 0 && !alloc_in) {
       if (p.G > DK)   // groups spanning heads: weights from the row maxima and Gamma
@@ -1092,7 +1100,10 @@ static hipError_t launch_interval_t(const KParams& p, hipStream_t st, int phases
     if (wb == WB_QUAD) return launch_chunk_requant(p, st);
     // d_k = 64: a wave of one lane per row would hold a whole head and pay the
     // longest scan of any of its rows; two lanes per row (2048 heads: 53 -> 44 us
-    // a step, 4096: 88 -> 70; at 128 two lanes are slower from 768 heads on)
+    // a step, 4096: 88 -> 70).  At 128 two lanes gain 4 to 6% with erasure at 288
+    // to 512 heads (four bits, 384: 44.4 -> 42.1), lose up to 4% there without at
+    // two to four bits (44.4 -> 45.5), and lose either way beyond (640: 48.8 ->
+    // 55.4, 1024: 57 -> 67)
     constexpr int PR = DK == 64 ? 2 : 1, NTH = requant_threads(DK, DV, PR);
     return c8 ? launch("requant", k_requant<DK, DV, true, true, PR>, nbh, NTH, 0, st, p)
               : launch("requant", k_requant<DK, DV, true, false, PR>, nbh, NTH, 0, st, p);
@@ -1141,7 +1152,10 @@ static hipError_t chunk_writeback(const KParams& p, int nsl, hipStream_t st, boo
   // with the selection of the widths when the keys are ready and the unit is a
   // sequence.  B = 1, H = 32, d = 128: 12.4 us per chunked interval instead of
   // the 18.3 of four lanes and two blocks per head; a second round of blocks
-  // would cost as much again
+  // would cost as much again.  d_k = 256, 128 tokens with two write-backs, one
+  // round and then a block of 512 threads per head (as here) against the decode
+  // step's three rounds and then 1024 threads: 48 heads 271 246 us, 64: 272 250,
+  // 96: 441 435, 128 to 320 heads within 0.5%
   const bool par = p.B * p.H * (DK / par_rows<DK>()) <= 256;
   if (par && keys && p.scope == 0) return launch_requant_par<DK, true>(p, st);
   if (keys && DK == 128 && !par) {
@@ -1197,16 +1211,18 @@ static hipError_t launch_pack_t(const KParams& p, const float* S, const uint8_t*
 
 // Lanes per row segment, blocks per head and staging by the number of heads
 // (us per call, one lane and block per head / two lanes, two blocks / four lanes,
-// two blocks, staged; d_k = 128, four bits):
-//   128 heads: 20.0 14.4 13.3   256: 20.7 19.1 18.4   512: 25.8 25.6 31.7
-//   768: 33.0 34.8 44.4   1024: 36.6 45.5 58.1
+// two blocks, staged; d_k = 128, a four-bit mean of [1, 8]):
+//   128 heads: 21.0 15.0 11.7   256: 21.9 19.4 15.5   288: 26.4 21.2 21.8
+//   512: 27.4 24.9 27.2   640: 32.2 28.0 33.7   768: 32.8 33.4 38.6
+//   1024: 36.7 41.0 50.0
 // Few heads are bound by the latency of a block's scan, many by instructions,
 // and the staged rows' LDS (33 KB) then keeps blocks off the compute units.
 // d_k = 64 (a wave of single lanes holds all 64 rows, and pays the longest scan
-// of any; one lane / two / four, staged): 256 heads: 18.9 13.2 10.8, 1024: 24.6
-// 18.0 16.5, 2048: 36.9 26.1 29.1.  d_k = 256: a thread per row segment (1024)
-// instead of two segments in turn (512) while a compute unit holds one block:
-// 41.3 -> 35.2 at 256 heads; 272: 58.3 against 65.0, 512: 59.9 against 68.0.
+// of any; one lane / two / four, staged): 256 heads: 20.5 14.4 10.2, 1024: 23.0
+// 18.1 15.4, 1280: 29.5 21.4 17.2, 2048: 35.2 25.9 27.0.  d_k = 256: a thread per
+// row segment (1024) instead of two segments in turn (512) while a compute unit
+// holds one block: 35.8 -> 34.2 at 256 heads; 272: 46.6 against 58.5, 512: 48.7
+// against 62.
 hipError_t launch_pack(const KParams& p, const float* S, const uint8_t* bits, const double* s_hat,
                        const double* r, unsigned ntok, hipStream_t st) {
   const int nbh = p.B * p.H;

@@ -174,11 +174,11 @@ __device__ __forceinline__ float segment_error(const float (&x)[SEG], float d, f
   return err;
 }
 
-// Quantise the rows of a row-major float32 state S[DK][DV] (device memory)
-// with widths bits[] (method: see the top of this file and include/kda.h).
-// Thread t handles the 64-column segment t % (DV/64) of row
-// perm[t / (DV/64)].  Writes int16 codes column-major into Ct[DV][CT_LD]
-// (LDS) and FP16 scales.
+// Quantise rows of a float32 state, a segment at a time as load_row(i, sg, x)
+// gives it, with widths bits[] (method: see the top of this file and
+// include/kda.h).  Thread t handles the 64-column segment t % (DV/64) of row
+// perm[t / (DV/64)].  Writes the codes column-major into the tile Ct (LDS; int8
+// or int16, ct_ld<DK, CT>() codes per column) and FP16 scales.
 //
 // Exact pruning: candidates are scanned from f = 1 downwards.  For m with
 // n Delta_m <= R the row maximum is coded as +-n, so its squared residual
@@ -370,7 +370,7 @@ __device__ __forceinline__ void fit_rows(LoadRow load_row, const uint8_t* bits, 
   }
 }
 
-// Pack codes Ct[DV][CT_LD] (column-major) with widths bits[] into column
+// Pack the codes of the column-major tile Ct with widths bits[] into column
 // bit streams, rows [r0, r0 + ROWS) of the head (a block may take part of a
 // head's rows).  Thread (column, half) packs half of those rows, starting at
 // bit P of its first row; the word both halves share (if the boundary is not
@@ -689,10 +689,9 @@ __device__ __forceinline__ void requant_head(const KParams& p, int bh, RequantLd
     auto quad = [&](int i, int sg, int k) {
       return load_staged_quad<DV>(sx, min(max(i - r0, 0), ROWS - 1), sg, k);
     };
-    if constexpr (STAGE && PAIRS > 1)
+    static_assert(!STAGE || PAIRS > 1, "staged rows: candidate lanes share a segment's codes");
+    if constexpr (STAGE)
       fit_rows<DK, DV, false, PAIRS, ROWS>(staged, sm.nb, sm.perm, sm.phi, sm.Ct, sm.sc16, p.diag_fit, quad);
-    else if constexpr (STAGE)
-      fit_rows<DK, DV, false, PAIRS, ROWS>(staged, sm.nb, sm.perm, sm.phi, sm.Ct, sm.sc16, p.diag_fit);
     else
       fit_rows<DK, DV, false, PAIRS, ROWS>(dense, sm.nb, sm.perm, sm.phi, sm.Ct, sm.sc16, p.diag_fit);
   }
@@ -711,7 +710,7 @@ using CodeTile = typename std::conditional<C8, int8_t, int16_t>::type;
 // takes a head (or half of one): one lane evaluates one of the 16 clip
 // factors of a 64-column segment, so the search is a single step of 64
 // elements per lane instead of up to 16 in turn, and a head is spread over
-// d_k / RQ_ROWS blocks of 1024 threads.  All factors are evaluated (the
+// d_k / par_rows<DK>() blocks of 1024 threads (one at d_k = 64).  All factors are evaluated (the
 // exhaustive search the pruned scans equal): 1.6 times the instructions of the
 // pruned search at d = 128, so only where the chip has room for them.  The
 // rows come from the float32 state of the statistics pass, in row order.
